@@ -5,6 +5,7 @@
 #include <cstring>
 #include <new>
 
+#include "group.h"
 #include "hphi_internal.h"
 
 using namespace hphi;
@@ -353,6 +354,25 @@ extern "C" int hphi_basis_build(const hphi_basis_desc* desc, hphi_basis** out) {
             }
         }
     }
+    // ---- order of the class-blocked product
+    if (d.sector != HPHI_SECTOR_NONE) {
+        GroupBasis& gb = B->grp;
+        std::vector<char> img;
+        group_order(B, h_val, h_lobase, cls_off, cls_count, gb, img);
+        if (int rc = dev_alloc(&gb.mem, img.size(), "hphi_basis_build: class order")) {
+            hphi_basis_free(B);
+            return rc;
+        }
+        const hipError_t eg = hipMemcpy(gb.mem, img.data(), img.size(), hipMemcpyHostToDevice);
+        if (eg != hipSuccess) {
+            hphi_basis_free(B);
+            return check_hip(eg, "hphi_basis_build: class order upload");
+        }
+        char* const at = static_cast<char*>(gb.mem);
+        gb.d_hord = reinterpret_cast<const uint32_t*>(at);
+        gb.d_cls = reinterpret_cast<const GClass*>(at + gb.cls_at);
+        for (int i = 0; i < 4; ++i) gb.d_groups[i] = reinterpret_cast<const GGroup*>(at + gb.groups_at[i]);
+    }
     *out = B;
     return HPHI_OK;
 }
@@ -368,6 +388,7 @@ extern "C" void hphi_basis_free(hphi_basis* b) {
     if (b->dmem) (void)hipFree(b->dmem);
     if (b->d_t1) (void)hipFree(b->d_t1);
     if (b->d_t1c) (void)hipFree(b->d_t1c);
+    if (b->grp.mem) (void)hipFree(b->grp.mem);
     delete b;
 }
 

@@ -1,0 +1,446 @@
+// Class-blocked sector product (group.h): the tables of a Hamiltonian, and the
+// choice of a kernel.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+
+#include "group.h"
+#include "hphi_internal.h"
+
+namespace hphi {
+
+int launch_hvg_f32(const HvgArgs& A, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
+int launch_hvg_f64(const HvgArgs& A, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
+int launch_hvg_multi_f32(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
+                         hipStream_t st);
+int launch_hvg_multi_f64(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
+                         hipStream_t st);
+
+namespace {
+
+// a sum with its rounding errors carried along (Knuth's two-sum)
+struct TwoSum {
+    double s = 0.0, e = 0.0;
+    __device__ void add(double x) {
+        const double t = s + x, b = t - s;
+        e += (s - (t - b)) + (x - b);
+        s = t;
+    }
+    __device__ double value() const { return s + e; }
+};
+
+// One thread per slot: its first row, the diagonal of the
+// high half, the partner blocks of the operators inside it, and per cross
+// operator the partner block and the signed element.
+__global__ __launch_bounds__(256) void group_high_kernel(GroupBuild G, BasisDev bs, const uint32_t* __restrict__ hord,
+                                                          uint32_t n_slot) {
+    const uint32_t p = blockIdx.x * 256u + threadIdx.x;
+    if (p >= n_slot) return;
+    const uint32_t k = hord[p];
+    const uint64_t h = bs.h_val[k];
+    const int64_t row0 = bs.h_row[k];
+    G.row0[p] = row0;
+    G.hval[p] = uint32_t(h);
+    TwoSum dhi;
+    for (int i = 0; i < G.n_dhi; ++i) {
+        const GBuildDiag& d = G.dhi[i];
+        const int bj = int((h >> (d.bj - bs.b_lo)) & 1);
+        const int bi = d.bi >= bs.b_lo ? int((h >> (d.bi - bs.b_lo)) & 1) : 0;
+        dhi.add(d.d[bi | (bj << 1)]);
+    }
+    G.dhi_out[p] = dhi.value();
+    uint32_t n = 0;
+    GEnt* hh = G.hh + size_t(p) * size_t(G.hh_stride);
+    for (int o = 0; o < G.n_hh; ++o) {
+        const GBuildOp& op = G.op_hh[o];
+        const uint64_t x = h & op.m_hi;
+        if (x == 0 || x == op.m_hi) continue;
+        const double s = (__popcll(h & op.sm_hi) & 1) ? -op.c : op.c;
+        hh[n++] = GEnt{bs.j_hi[h ^ op.m_hi], s};
+    }
+    G.n_ent[p] = n;
+    for (; n < uint32_t(G.hh_stride); ++n) hh[n] = GEnt{row0, 0.0};
+    for (int o = 0; o < G.n_lh; ++o) {
+        const GBuildOp& op = G.op_lh[o];
+        const int64_t t = bs.j_hi[h ^ op.m_hi];
+        // no sector state has the target high half: then no row of h is live
+        const uint64_t sg = uint64_t(__popcll(h & op.sm_hi) & 1) << 63;
+        G.lhe[size_t(o) * n_slot + p] = int64_t(uint64_t(t >= 0 ? t : row0) | sg);
+    }
+    for (int c = 0; c < G.n_ci; ++c) {
+        TwoSum w;
+        for (int i = 0; i < G.n_x; ++i) {
+            if (G.dx[i].ci != c) continue;
+            const bool up = ((h >> (G.dx[i].bj - bs.b_lo)) & 1) != 0;
+            if (up) w.add(G.dx[i].d[3]);
+            else if (G.dx[i].spin) w.add(-G.dx[i].d[3]);
+        }
+        G.w[size_t(c) * n_slot + p] = w.value();
+    }
+}
+
+// one thread per low half: its diagonal, its partner list and the partners of
+// its single flips
+__global__ __launch_bounds__(256) void group_low_kernel(GroupBuild G, BasisDev bs) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t n_low = 1u << bs.b_lo;
+    if (i >= n_low) return;
+    const uint32_t l = bs.lows[i];
+    TwoSum s;
+    for (int k = 0; k < G.n_dlo; ++k) {
+        const GBuildDiag& d = G.dlo_ops[k];
+        const int bi = int((l >> d.bi) & 1u);
+        const int bj = d.bj < bs.b_lo ? int((l >> d.bj) & 1u) : 0;
+        s.add(d.d[bi | (bj << 1)]);
+    }
+    G.dlo[i] = s.value();
+    for (int o = 0; o < G.n_ll; ++o) {
+        const GLow op = G.ll[o];
+        const uint32_t x = l & op.m;
+        const uint32_t ci = uint32_t((__popc(l & op.sm) & 1) ? op.neg : op.pos);
+        G.nbr[size_t(o) * n_low + i] = x == 0 || x == op.m ? bs.j_lo[l] : bs.j_lo[l ^ op.m] | (ci << 24);
+    }
+    const int rows = (G.n_ll + kGroupPad - 1) / kGroupPad * kGroupPad;
+    for (int o = G.n_ll; o < rows; ++o) G.nbr[size_t(o) * n_low + i] = bs.j_lo[l];
+    for (int k = 0; k < G.n_col; ++k) {
+        const GColumn col = G.col[k];
+        const uint32_t sg = uint32_t(__popc(l & col.sm) & 1) << 30, bit = (l & col.mi) ? 0x80000000u : 0u;
+        G.xnb[size_t(k) * n_low + i] = bs.j_lo[l ^ col.mi] | sg | bit;
+    }
+}
+
+int cu_count() {
+    static const int n = [] {
+        int dev = 0, ncu = 0;
+        (void)hipGetDevice(&dev);
+        if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 256;
+        return ncu;
+    }();
+    return n;
+}
+
+}  // namespace
+
+// Sort the operators of a Hamiltonian by the halves they touch.  Operators
+// that are not a real symmetric flip of two bits with the charge kept (complex
+// elements, row conditions, a sign mask that mixes a one-half flip with the
+// other half) leave the whole Hamiltonian to the per-tile kernel.
+bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_complex, bool has_cond, GroupHost& out) {
+    if (B->dev.sector == 0 || !B->grp.d_hord || is_complex || has_cond) return false;
+    const int b_lo = B->b_lo;
+    const uint64_t ml = (uint64_t(1) << b_lo) - 1;
+    struct Cross {
+        uint32_t mi, sm;
+        int j;
+        GBuildOp b;
+    };
+    std::vector<Cross> lh;
+    out.coef.assign(1, 0.0);
+    auto coef_at = [&](double c) {
+        for (size_t k = 0; k < out.coef.size(); ++k)
+            if (out.coef[k] == c) return int32_t(k);
+        out.coef.push_back(c);
+        return int32_t(out.coef.size() - 1);
+    };
+    for (size_t o = 0; o < ops.size(); ++o) {
+        const DevOp& op = ops[o];
+        if (op.has_off) {
+            if (op.bi == op.bj || op.xmask != ((uint64_t(1) << op.bi) | (uint64_t(1) << op.bj))) return false;
+            if (op.cr[0] != 0.0 || op.cr[3] != 0.0 || op.cr[1] != op.cr[2]) return false;
+            const uint64_t xl = op.xmask & ml, xh = op.xmask >> b_lo, sl = op.smask & ml, sh = op.smask >> b_lo;
+            if (xh == 0) {
+                if (sh) return false;
+                out.ll.push_back(GLow{uint32_t(xl), uint32_t(sl), coef_at(op.cr[1]), coef_at(-op.cr[1]), int32_t(o), 0});
+            } else if (xl == 0) {
+                if (sl) return false;
+                out.hh.push_back(GBuildOp{xh, sh, op.cr[1], int32_t(o), 0});
+            } else {
+                lh.push_back({uint32_t(xl), uint32_t(sl), __builtin_ctzll(xh), GBuildOp{xh, sh, op.cr[1], int32_t(o), 0}});
+            }
+        }
+        if (op.d[0] == 0.0 && op.d[1] == 0.0 && op.d[2] == 0.0 && op.d[3] == 0.0) continue;
+        GBuildDiag d{int(op.bi), int(op.bj), -1, 0, {op.d[0], op.d[1], op.d[2], op.d[3]}};
+        const bool li = int(op.bi) < b_lo, lj = int(op.bj) < b_lo;
+        if (li && lj) out.dlo.push_back(d);
+        else if (!li && !lj) out.dhi.push_back(d);
+        else {
+            if (!li) {   // the low bit first
+                std::swap(d.bi, d.bj);
+                std::swap(d.d[1], d.d[2]);
+            }
+            // split into parts of one bit each and a product term.  Where the
+            // two bits enter as spins (d0 == d3, d1 == d2) the product of the
+            // signs +-1 carries all but a constant, so no large parts cancel:
+            //   d = (d0 + d1) / 2 + (d0 - d1) / 2 * (2 bi - 1) (2 bj - 1);
+            // otherwise
+            //   d = d0 + (d1 - d0) bi + (d2 - d0) bj + (d3 - d2 - d1 + d0) bi bj
+            const double d0 = d.d[0], d1 = d.d[1], d2 = d.d[2], d3 = d.d[3];
+            const bool spin = d0 == d3 && d1 == d2;
+            double dx = (d3 - d2) - (d1 - d0);
+            if (spin) {
+                dx = 0.5 * (d0 - d1);
+                const double c0 = 0.5 * (d0 + d1);
+                if (c0 != 0.0) out.dhi.push_back(GBuildDiag{d.bj, d.bj, -1, 0, {c0, 0.0, 0.0, c0}});
+            } else {
+                out.dlo.push_back(GBuildDiag{d.bi, d.bi, -1, 0, {0.0, 0.0, 0.0, d1 - d0}});
+                out.dhi.push_back(GBuildDiag{d.bj, d.bj, -1, 0, {d0, 0.0, 0.0, d2}});
+            }
+            if (dx != 0.0) {
+                const uint32_t key = uint32_t(d.bi) | (spin ? 32u : 0u);
+                int col = -1;
+                for (size_t q = 0; q < out.ci.size(); ++q)
+                    if (out.ci[q] == key) col = int(q);
+                if (col < 0) {
+                    col = int(out.ci.size());
+                    out.ci.push_back(key);
+                }
+                out.dx.push_back(GBuildDiag{d.bi, d.bj, col, spin ? 1 : 0, {0.0, 0.0, 0.0, dx}});
+            }
+        }
+    }
+    if (out.coef.size() > size_t(kGroupCoef)) return false;
+    // one column per low bit and sign mask, its operators next to each other
+    std::vector<char> done(lh.size(), 0);
+    for (size_t a = 0; a < lh.size(); ++a) {
+        if (done[a]) continue;
+        for (size_t b = a; b < lh.size(); ++b) {
+            if (done[b] || lh[b].mi != lh[a].mi || lh[b].sm != lh[a].sm) continue;
+            done[b] = 1;
+            out.lh.push_back(GCross{lh[b].j, int32_t(out.col.size()), lh[b].b.op, 0, lh[b].b.c});
+            out.lh_build.push_back(lh[b].b);
+        }
+        out.col.push_back(GColumn{lh[a].mi, lh[a].sm});
+    }
+    while (out.lh.size() % size_t(kGroupPad)) {
+        out.lh.push_back(GCross{0, 0, -1, 0, 0.0});
+        out.lh_build.push_back(GBuildOp{0, 0, 0.0, -1, 0});
+    }
+    // the tables stay below half of an 8-byte vector, or small
+    const size_t n_low = size_t(1) << b_lo, n_slot = size_t(B->grp.n_slot);
+    const size_t bytes = n_slot * (24 + 16 * out.hh.size() + 8 * (out.lh.size() + out.ci.size())) +
+                         n_low * (8 + 4 * (out.ll.size() + out.col.size()));
+    if (bytes > (size_t(16) << 20) && bytes > size_t(B->dim) * 4) return false;
+    return true;
+}
+
+// Order the high halves and deal their groups to the XCDs.  The top bits of
+// the high half come first: a segment of them holds at most about 96 MB of an
+// 8-byte vector, so the partner blocks of the operators on the other bits stay
+// in the 256 MB memory-side cache while the eight XCDs sweep the segment
+// together; inside it the charge classes, and inside a class ascending high
+// halves in groups of K.  A group goes to the XCD with the fewest items so far,
+// whole, so that the blocks of a group are read through one L2.
+void group_order(const hphi_basis* B, const std::vector<uint64_t>& h_val, const std::vector<uint32_t>& h_lobase,
+                 const std::vector<uint32_t>& cls_off, const std::vector<uint32_t>& cls_count, GroupBasis& gb,
+                 std::vector<char>& image) {
+    const int ncls = int(cls_count.size());
+    const size_t n_high = h_val.size();
+    int seg = 0;
+    while (seg < 12 && seg < B->b_hi - 8 && ((B->dim * 8) >> seg) > (int64_t(96) << 20)) ++seg;
+    if (const char* e = std::getenv("HPHI_GROUP_SEG")) seg = std::min(B->b_hi, std::max(0, std::atoi(e)));
+    const int shift = B->b_hi - seg;
+    std::vector<int> cls_of(size_t(cls_off[size_t(ncls)]) + 1, 0);
+    for (int c = 0; c < ncls; ++c)
+        if (cls_count[size_t(c)]) cls_of[cls_off[size_t(c)]] = c;
+    std::vector<GClass> cls;
+    std::vector<int> slot(size_t(ncls), -1);
+    std::vector<char> used(size_t(ncls), 0);
+    for (size_t k = 0; k < n_high; ++k) used[size_t(cls_of[h_lobase[k]])] = 1;
+    for (int c = 0; c < ncls; ++c) {
+        if (!used[size_t(c)]) continue;
+        slot[size_t(c)] = int(cls.size());
+        const uint32_t nt = (cls_count[size_t(c)] + 63) / 64;
+        cls.push_back(GClass{cls_off[size_t(c)], cls_count[size_t(c)], nt, 0});
+    }
+    gb.n_cls = int(cls.size());
+    // segments of equal top bits are contiguous (h_val ascends)
+    struct Run {
+        uint32_t p0, n, cls;
+    };
+    std::vector<Run> runs;
+    std::vector<uint32_t> hord;
+    hord.reserve(n_high + n_high / 8);
+    std::vector<std::vector<uint32_t>> of_cls(cls.size());
+    for (size_t a = 0; a < n_high;) {
+        size_t b = a;
+        for (; b < n_high && (h_val[b] >> shift) == (h_val[a] >> shift); ++b)
+            of_cls[size_t(slot[size_t(cls_of[h_lobase[b]])])].push_back(uint32_t(b));
+        for (size_t c = 0; c < cls.size(); ++c) {
+            std::vector<uint32_t>& o = of_cls[c];
+            if (o.empty()) continue;
+            runs.push_back(Run{uint32_t(hord.size()), uint32_t(o.size()), uint32_t(c)});
+            hord.insert(hord.end(), o.begin(), o.end());
+            while (hord.size() % size_t(kGroupSlots)) hord.push_back(o.back());
+            o.clear();
+        }
+        a = b;
+    }
+    gb.n_slot = uint32_t(hord.size());
+    auto put = [&](const void* src, size_t bytes) {
+        const size_t o = image.size();
+        image.resize(o + (bytes + 255) / 256 * 256);
+        std::copy_n(static_cast<const char*>(src), bytes, image.data() + o);
+        return o;
+    };
+    put(hord.data(), hord.size() * 4);
+    gb.cls_at = put(cls.data(), cls.size() * sizeof(GClass));
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t K = 1u << i;
+        std::vector<GGroup> of[8];
+        uint32_t items[8] = {};
+        for (const Run& r : runs)
+            for (uint32_t k = 0; k < r.n; k += K) {
+                const int x = int(std::min_element(items, items + 8) - items);
+                of[x].push_back(GGroup{items[x], r.p0 + k, r.cls, std::min(K, r.n - k)});
+                items[x] += cls[r.cls].n_tile;
+            }
+        std::vector<GGroup> all;
+        for (int x = 0; x < 8; ++x) {
+            gb.begin[i][x] = uint32_t(all.size());
+            gb.items[i][x] = items[x];
+            all.insert(all.end(), of[x].begin(), of[x].end());
+            all.push_back(GGroup{items[x], 0, 0, 0});
+        }
+        gb.begin[i][8] = uint32_t(all.size());
+        gb.groups_at[i] = put(all.data(), all.size() * sizeof(GGroup));
+    }
+}
+
+int group_build(const hphi_basis* B, const GroupBuild& G) {
+    const uint32_t n_slot = B->grp.n_slot;
+    group_high_kernel<<<(n_slot + 255) / 256, 256, 0, nullptr>>>(G, B->dev, B->grp.d_hord, n_slot);
+    int rc = check_hip(hipGetLastError(), "group_high launch");
+    if (rc) return rc;
+    group_low_kernel<<<((1u << B->b_lo) + 255) / 256, 256, 0, nullptr>>>(G, B->dev);
+    rc = check_hip(hipGetLastError(), "group_low launch");
+    return rc ? rc : check_hip(hipStreamSynchronize(nullptr), "hphi_ham_build: sector tables");
+}
+
+// High halves per wavefront.  More of them share one decode and put more
+// gathers in flight, but leave fewer wavefronts.
+static int group_k(int ns, int dtype, int64_t rows) {
+    if (const char* e = std::getenv("HPHI_GROUP_K")) {
+        const int k = std::atoi(e);
+        if (k == 1 || k == 2 || k == 4 || (k == 8 && ns <= 2)) return k;
+    }
+    if (rows >= (int64_t(1) << 22)) return ns <= 2 ? 8 : 4;
+    return rows >= (int64_t(1) << 19) ? 4 : 2;
+}
+
+static void group_args(const hphi_ham* H, int k, bool cplx, HvgArgs& A) {
+    const GroupBasis& g = H->basis->grp;
+    const int i = k == 8 ? 3 : k == 4 ? 2 : k == 2 ? 1 : 0;
+    A.plan = *H->grp;
+    A.grp.groups = g.d_groups[i];
+    for (int x = 0; x < 9; ++x) A.grp.begin[x] = g.begin[i][x];
+    for (int x = 0; x < 8; ++x) A.grp.items[x] = g.items[i][x];
+    A.cls = g.d_cls;
+    A.lows = H->basis->dev.lows;
+    A.cshift = cplx ? 1 : 0;
+}
+
+int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
+    const hphi_ham* H = L.ham;
+    const hphi_basis* B = H->basis;
+    if (!H->grp || sc.sector_blocks != 2 || (B->nbits > 32 && L.nvec > 4)) return 1;
+    const bool cplx = dtype_complex(L.dtype), f64 = L.dtype == HPHI_F64 || L.dtype == HPHI_C128;
+    if (L.ex && !cplx) return 1;
+    const int ns = L.nvec * (cplx ? 2 : 1);
+    const int k = group_k(ns, L.dtype, B->dim);
+    HvgArgs A{};
+    group_args(H, k, cplx, A);
+    A.v = L.v;
+    A.u = L.u;
+    A.y = L.y;
+    A.cy = L.cy;
+    A.sx = L.sx;
+    A.a = L.a;
+    A.b = L.b;
+    A.stop = L.stop;
+    A.partials = H->d_partials;
+    if (L.ex) A.ex = *L.ex;
+    int grid = 0;
+    const bool sign = B->desc.particle == HPHI_FERMION;
+    const int rc = f64 ? launch_hvg_f64(A, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
+                       : launch_hvg_f32(A, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
+    if (rc || L.ex || !L.reduce_out) return rc;
+    return launch_product_reduce(H, grid, L.nvec, L, st);
+}
+
+// Several problems that all have the class-blocked tables: the problems share
+// the grid in proportion to their wavefront items.
+int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
+    const int dtype = Ls[0].dtype;
+    for (int p = 0; p < n; ++p)
+        if (!Ls[p].ham->grp || schedule_for(Ls[p].ham, 1, dtype).sector_blocks != 2) return 1;
+    const bool cplx = dtype_complex(dtype), f64 = dtype == HPHI_F64 || dtype == HPHI_C128;
+    const int ns = cplx ? 2 : 1;
+    MultiPlan P;
+    P.n = n;
+    P.dtype = dtype;
+    int64_t rows = 0;
+    for (int p = 0; p < n; ++p) rows += Ls[p].ham->basis->dim;
+    P.group_k = group_k(ns, dtype, rows);
+    P.cc = false;
+    std::vector<HvgArgs> args(n, HvgArgs{});
+    std::vector<int64_t> items(n);
+    for (int p = 0; p < n; ++p) {
+        const HvLaunch& L = Ls[p];
+        HvgArgs& A = args[p];
+        group_args(L.ham, P.group_k, cplx, A);
+        items[p] = 0;
+        for (int x = 0; x < 8; ++x) items[p] += A.grp.items[x];
+        P.sign = P.sign || L.ham->basis->desc.particle == HPHI_FERMION;
+        A.v = L.v;
+        A.u = L.u;
+        A.y = L.y;
+        A.cy = L.cy;
+        A.sx = L.sx;
+        A.a = L.a;
+        A.b = L.b;
+        A.stop = L.stop;
+    }
+    int occ = 1;
+    if (int rc = f64 ? launch_hvg_multi_f64(nullptr, nullptr, n, ns, P.group_k, P.sign, 0, &occ, nullptr)
+                     : launch_hvg_multi_f32(nullptr, nullptr, n, ns, P.group_k, P.sign, 0, &occ, nullptr))
+        return rc;
+    const std::vector<int> begin = deal_blocks(items, int64_t(std::max(1, occ)) * cu_count() / 8);
+    P.grid = begin[n];
+    const size_t a_bytes = size_t(n) * sizeof(HvgArgs);
+    const size_t b_off = (a_bytes + 255) / 256 * 256;
+    const size_t p_off = b_off + (size_t(n + 1) * 4 + 255) / 256 * 256;
+    const size_t r_off = p_off + size_t(P.grid) * kNQ * sizeof(double);
+    const size_t total = r_off + size_t(n) * sizeof(RedDesc);
+    char* mem = nullptr;
+    if (int rc = dev_alloc((void**)&mem, total, "hv_multi_prepare")) return rc;
+    std::vector<RedDesc> red(n);
+    double* partials = reinterpret_cast<double*>(mem + p_off);
+    for (int p = 0; p < n; ++p) {
+        args[p].partials = partials + size_t(begin[p]) * kNQ;
+        red[p] = RedDesc{args[p].partials, begin[p + 1] - begin[p], 0, Ls[p].reduce_out, Ls[p].stop, Ls[p].ham->d_flag};
+    }
+    hipError_t e = hipMemcpy(mem, args.data(), a_bytes, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(mem + b_off, begin.data(), size_t(n + 1) * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(mem + r_off, red.data(), size_t(n) * sizeof(RedDesc), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(mem);
+        return check_hip(e, "hv_multi_prepare: upload");
+    }
+    P.mem = mem;
+    P.d_args = mem;
+    P.d_begin = reinterpret_cast<const int*>(mem + b_off);
+    P.d_red = reinterpret_cast<const RedDesc*>(mem + r_off);
+    *out = P;
+    return HPHI_OK;
+}
+
+int group_multi_launch(const MultiPlan& P, hipStream_t st) {
+    const HvgArgs* a = static_cast<const HvgArgs*>(P.d_args);
+    const int ns = dtype_complex(P.dtype) ? 2 : 1;
+    return P.dtype == HPHI_F64 || P.dtype == HPHI_C128
+               ? launch_hvg_multi_f64(a, P.d_begin, P.n, ns, P.group_k, P.sign, P.grid, nullptr, st)
+               : launch_hvg_multi_f32(a, P.d_begin, P.n, ns, P.group_k, P.sign, P.grid, nullptr, st);
+}
+
+}  // namespace hphi

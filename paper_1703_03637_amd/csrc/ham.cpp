@@ -3,9 +3,11 @@
 #include <algorithm>
 #include <cmath>
 #include <complex>
+#include <cstring>
 #include <new>
 #include <vector>
 
+#include "group.h"
 #include "hphi_internal.h"
 
 using namespace hphi;
@@ -316,26 +318,145 @@ extern "C" int hphi_ham_build(const hphi_basis* basis, const hphi_term* terms, i
             ptab[size_t(o) * 16 + q * 4 + 1] = padded[o].has_off ? padded[o].ci[q] : 0.0;
             ptab[size_t(o) * 16 + q * 4 + 2] = padded[o].d[q];
         }
-    const size_t ops_bytes = padded.size() * sizeof(DevOp);
-    const size_t ptab_bytes = ptab.size() * sizeof(double);
-    const size_t part_bytes = size_t(kMaxGrid) * kNQ * kMaxNvec * sizeof(double);
-    // reductions, then the non-finite flag word in the same allocation
-    const size_t red_bytes = size_t(kNQ) * kMaxNvec * sizeof(double) + 256;
-    int rc = dev_alloc((void**)&H->d_partials, part_bytes, "hphi_ham_build: partials");
-    if (!rc) rc = dev_alloc((void**)&H->d_red, red_bytes, "hphi_ham_build: reductions");
-    if (!rc) rc = dev_alloc((void**)&H->d_ops, ops_bytes, "hphi_ham_build: operators");
-    if (!rc) rc = dev_alloc((void**)&H->d_ptab, ptab_bytes, "hphi_ham_build: pattern table");
-    if (rc) {
+    // One allocation: reduction partials, reductions and the non-finite flag
+    // word, then what is uploaded (operators, pattern table and, for the
+    // class-blocked sector product, its operator lists), then that product's
+    // tables, filled by a kernel.
+    GroupHost gh;
+    const bool grouped = group_analyse(basis, ops, is_complex, H->has_cond, gh);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    const size_t o_part = take(size_t(kMaxGrid) * kNQ * kMaxNvec * sizeof(double));
+    const size_t o_up = off;
+    const size_t o_red = take(size_t(kNQ) * kMaxNvec * sizeof(double) + 256);
+    const size_t o_ops = take(padded.size() * sizeof(DevOp));
+    const size_t o_ptab = take(ptab.size() * sizeof(double));
+    const size_t base_bytes = off;
+    const size_t n_slot = size_t(basis->grp.n_slot);
+    const size_t n_low = size_t(1) << basis->b_lo;
+    const size_t n_hh = gh.hh.size(), n_lh = gh.lh.size(), n_ci = gh.ci.size(), n_ll = gh.ll.size(), n_col = gh.col.size();
+    const size_t stride = (n_hh + kGroupEnt - 1) / kGroupEnt * kGroupEnt;
+    const size_t ll_rows = (n_ll + kGroupPad - 1) / kGroupPad * kGroupPad;
+    const size_t o_ll = take(n_ll * sizeof(GLow)), o_coef = take(gh.coef.size() * 8), o_col = take(n_col * sizeof(GColumn)),
+                 o_lh = take(n_lh * sizeof(GCross)), o_ci = take(n_ci * 4), o_bhh = take(n_hh * sizeof(GBuildOp)),
+                 o_blh = take(n_lh * sizeof(GBuildOp)), o_dlo = take(gh.dlo.size() * sizeof(GBuildDiag)),
+                 o_dhi = take(gh.dhi.size() * sizeof(GBuildDiag)), o_dx = take(gh.dx.size() * sizeof(GBuildDiag));
+    const size_t up_end = off;
+    const size_t o_row = take(n_slot * 8), o_hv = take(n_slot * 4), o_ne = take(n_slot * 4), o_dh = take(n_slot * 8),
+                 o_hh = take(n_slot * stride * sizeof(GEnt)), o_lhe = take(n_lh * n_slot * 8),
+                 o_w = take(n_ci * n_slot * sizeof(double)),
+                 o_dl = take(n_low * sizeof(double)), o_nbr = take(ll_rows * n_low * 4), o_xnb = take(n_col * n_low * 4);
+    bool group = grouped;
+    if (alloc_fails()) {
         hphi_ham_free(H);
-        return rc;
+        return set_error(HPHI_ENOMEM, "hphi_ham_build: device allocation failed (injected)");
     }
+    hipError_t e = hipMalloc(&H->d_mem, group ? off : base_bytes);
+    if (e == hipErrorOutOfMemory && group) {   // without the class-blocked tables
+        (void)hipGetLastError();
+        group = false;
+        e = hipMalloc(&H->d_mem, base_bytes);
+    }
+    if (e != hipSuccess) {
+        H->d_mem = nullptr;
+        (void)hipGetLastError();
+        hphi_ham_free(H);
+        return set_error(e == hipErrorOutOfMemory ? HPHI_ENOMEM : HPHI_EDEVICE, "hphi_ham_build: device allocation of %zu bytes: %s",
+                         base_bytes, hipGetErrorString(e));
+    }
+    char* const m = static_cast<char*>(H->d_mem);
+    H->d_partials = reinterpret_cast<double*>(m + o_part);
+    H->d_red = reinterpret_cast<double*>(m + o_red);
     H->d_flag = reinterpret_cast<int32_t*>(H->d_red + kNQ * kMaxNvec);
-    hipError_t e = hipMemcpy(H->d_ops, padded.data(), ops_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(H->d_flag, 0, sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemcpy(H->d_ptab, ptab.data(), ptab_bytes, hipMemcpyHostToDevice);
+    H->d_ops = reinterpret_cast<DevOp*>(m + o_ops);
+    H->d_ptab = reinterpret_cast<double*>(m + o_ptab);
+    const size_t up_bytes = (group ? up_end : base_bytes) - o_up;
+    std::vector<char> up(up_bytes, 0);         // the reductions and the flag start at zero
+    auto fill = [&](size_t at, const void* src, size_t bytes) {
+        if (bytes) std::memcpy(up.data() + (at - o_up), src, bytes);
+    };
+    fill(o_ops, padded.data(), padded.size() * sizeof(DevOp));
+    fill(o_ptab, ptab.data(), ptab.size() * sizeof(double));
+    if (group) {
+        fill(o_ll, gh.ll.data(), n_ll * sizeof(GLow));
+        fill(o_coef, gh.coef.data(), gh.coef.size() * 8);
+        fill(o_col, gh.col.data(), n_col * sizeof(GColumn));
+        fill(o_lh, gh.lh.data(), n_lh * sizeof(GCross));
+        fill(o_ci, gh.ci.data(), n_ci * 4);
+        fill(o_bhh, gh.hh.data(), n_hh * sizeof(GBuildOp));
+        fill(o_blh, gh.lh_build.data(), n_lh * sizeof(GBuildOp));
+        fill(o_dlo, gh.dlo.data(), gh.dlo.size() * sizeof(GBuildDiag));
+        fill(o_dhi, gh.dhi.data(), gh.dhi.size() * sizeof(GBuildDiag));
+        fill(o_dx, gh.dx.data(), gh.dx.size() * sizeof(GBuildDiag));
+    }
+    e = hipMemcpy(m + o_up, up.data(), up_bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         hphi_ham_free(H);
         return check_hip(e, "hphi_ham_build: upload");
+    }
+    if (group) {
+        GroupBuild G{};
+        G.op_hh = reinterpret_cast<const GBuildOp*>(m + o_bhh);
+        G.op_lh = reinterpret_cast<const GBuildOp*>(m + o_blh);
+        G.dlo_ops = reinterpret_cast<const GBuildDiag*>(m + o_dlo);
+        G.dhi = reinterpret_cast<const GBuildDiag*>(m + o_dhi);
+        G.dx = reinterpret_cast<const GBuildDiag*>(m + o_dx);
+        G.n_hh = int(n_hh);
+        G.n_lh = int(n_lh);
+        G.n_dlo = int(gh.dlo.size());
+        G.n_dhi = int(gh.dhi.size());
+        G.n_x = int(gh.dx.size());
+        G.n_ci = int(n_ci);
+        G.hh_stride = int(stride);
+        G.n_ll = int(n_ll);
+        G.n_col = int(n_col);
+        G.ll = reinterpret_cast<const GLow*>(m + o_ll);
+        G.col = reinterpret_cast<const GColumn*>(m + o_col);
+        G.row0 = reinterpret_cast<int64_t*>(m + o_row);
+        G.hval = reinterpret_cast<uint32_t*>(m + o_hv);
+        G.n_ent = reinterpret_cast<uint32_t*>(m + o_ne);
+        G.dhi_out = reinterpret_cast<double*>(m + o_dh);
+        G.hh = reinterpret_cast<GEnt*>(m + o_hh);
+        G.lhe = reinterpret_cast<int64_t*>(m + o_lhe);
+        G.w = reinterpret_cast<double*>(m + o_w);
+        G.dlo = reinterpret_cast<double*>(m + o_dl);
+        G.nbr = reinterpret_cast<uint32_t*>(m + o_nbr);
+        G.xnb = reinterpret_cast<uint32_t*>(m + o_xnb);
+        H->grp = new (std::nothrow) GroupPlan();
+        const int rc = H->grp ? group_build(basis, G) : set_error(HPHI_ENOMEM, "hphi_ham_build: host allocation");
+        if (rc) {
+            hphi_ham_free(H);
+            return rc;
+        }
+        GroupPlan& P = *H->grp;
+        P.n_ll = int(n_ll);
+        P.n_lh = int(n_lh);
+        P.n_col = int(n_col);
+        P.n_ci = int(n_ci);
+        P.n_hh = int(n_hh);
+        P.n_coef = int(gh.coef.size());
+        P.hh_stride = int(stride);
+        P.n_slot = uint32_t(n_slot);
+        P.n_low = uint32_t(n_low);
+        P.row0 = G.row0;
+        P.hval = G.hval;
+        P.n_ent = G.n_ent;
+        P.dhi = G.dhi_out;
+        P.hh = G.hh;
+        P.lhe = G.lhe;
+        P.w = G.w;
+        P.ci = reinterpret_cast<const uint32_t*>(m + o_ci);
+        P.dlo = G.dlo;
+        P.nbr = G.nbr;
+        P.xnb = G.xnb;
+        P.coef = reinterpret_cast<const double*>(m + o_coef);
+        P.lh = reinterpret_cast<const GCross*>(m + o_lh);
+        P.ll_ops = G.ll;
+        P.hh_ops = G.op_hh;
     }
     // persistent grid: enough waves to cover the tiles, at most kMaxGrid blocks,
     // a multiple of 8 so every XCD gets the same number of blocks
@@ -355,10 +476,8 @@ extern "C" int hphi_ham_is_complex(const hphi_ham* h, int32_t* is_complex) {
 }
 
 hphi_ham::~hphi_ham() {
-    if (d_ops) (void)hipFree(d_ops);
-    if (d_ptab) (void)hipFree(d_ptab);
-    if (d_partials) (void)hipFree(d_partials);
-    if (d_red) (void)hipFree(d_red);
+    if (d_mem) (void)hipFree(d_mem);
+    delete grp;
     for (PassPlan* p : plans) {
         if (p->d_ops) (void)hipFree(p->d_ops);
         if (p->d_perm) (void)hipFree(p->d_perm);

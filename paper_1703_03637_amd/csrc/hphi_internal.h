@@ -61,8 +61,8 @@ struct Schedule {
                             // (spaces wider than 32 bits: 1 = the two-level low-rank table in LDS,
                             // 2 = only the pattern table, the full low table read through the caches)
     int nt_streams = 0;     // windowed kernel: non-temporal hints on partial sums, output and staged copies
-    int sector_blocks = 0;  // sector bases: 1 = block-staged kernel (high-half blocks in LDS), 0 = the
-                            // per-tile kernel (measured as fast or faster on every workload here)
+    int sector_blocks = 2;  // sector bases: 2 = class-blocked kernel where the Hamiltonian has its tables (else the
+                            // per-tile kernel), 1 = block-staged kernel (high-half blocks in LDS), 0 = per-tile kernel
 };
 
 // Compact kernel-side operator of the windowed product (configurations of
@@ -145,6 +145,25 @@ struct BasisDev {
     const uint32_t* lows;     // low halves grouped by charge class, ascending
 };
 
+struct GClass;
+struct GGroup;
+struct GroupPlan;
+
+// Order of a sector basis for the class-blocked product (group.h): the valid
+// high halves in the order of their groups, the charge classes, and the groups
+// for K = 1, 2, 4 and 8 high halves per wavefront.
+struct GroupBasis {
+    void* mem = nullptr;
+    const uint32_t* d_hord = nullptr;  // [n_slot] valid-high index of each slot
+    uint32_t n_slot = 0;
+    const GClass* d_cls = nullptr;
+    int n_cls = 0;
+    const GGroup* d_groups[4] = {};
+    uint32_t begin[4][9] = {};         // groups of each XCD (with one closing entry each)
+    uint32_t items[4][8] = {};         // wavefront items of each XCD
+    size_t cls_at = 0, groups_at[4] = {};
+};
+
 }  // namespace hphi
 
 struct hphi_basis {
@@ -173,6 +192,7 @@ struct hphi_basis {
     uint32_t* d_t1 = nullptr;     // [2^(b_lo - lr_b2)][lr_ncls]
     uint16_t* d_t2 = nullptr;     // [2^lr_b2]
     size_t lr_bytes = 0;          // bytes of T1 and T2 as the kernel stages them
+    hphi::GroupBasis grp;         // class order (sector bases)
 };
 
 struct hphi_ham {
@@ -182,6 +202,8 @@ struct hphi_ham {
     bool is_complex = false;
     bool has_cond = false;        // some operator carries a row condition (cmask)
     std::vector<hphi::DevOp> ops;
+    void* d_mem = nullptr;         // one allocation: everything below up to the class-blocked tables
+    hphi::GroupPlan* grp = nullptr;              // class-blocked tables (host copy of the device view), or null
     hphi::DevOp* d_ops = nullptr;  // ops padded with inert entries to n_ops_pad
     int n_ops_pad = 0;            // multiple of 4
     double* d_ptab = nullptr;     // [n_ops_pad][4 patterns][Re c, Im c, d, 0]
@@ -344,6 +366,8 @@ struct MultiPlan {
     bool gtab = false;
     int dtype = 0;
     bool cc = false, sector = false, w64 = false;
+    bool sign = false;       // class-blocked kernel: fermion signs
+    int group_k = 0;         // > 0: class-blocked kernel with this many high halves per wavefront
     void* mem = nullptr;     // device: args, begin, partials, reductions
     const void* d_args = nullptr;
     const int* d_begin = nullptr;
@@ -361,7 +385,18 @@ struct LzMulti {
     const double* evec;
     int stride;
 };
+// blocks of a persistent grid dealt to problems in multiples of 8: begin[n + 1]
+// from the wavefront items of each (`groups`: groups of 8 blocks in all)
+std::vector<int> deal_blocks(const std::vector<int64_t>& items, int64_t groups);
+// the sums of a product from its block partials
+int launch_product_reduce(const hphi_ham* H, int n_parts, int B, const HvLaunch& L, hipStream_t st);
 int hv_multi_launch(const MultiPlan& P, const LzMulti* lz, hipStream_t st);
+// the class-blocked product when the Hamiltonian has its tables and the
+// schedule asks for it; 1 if not
+int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st);
+// the same for several problems in one launch
+int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out);
+int group_multi_launch(const MultiPlan& P, hipStream_t st);
 struct UpdPlan {
     int n = 0;
     int grid = 0;

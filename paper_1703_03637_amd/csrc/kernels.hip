@@ -28,17 +28,10 @@
 #include <type_traits>
 
 #include "hphi_internal.h"
+#include "lane.h"
 
 namespace hphi {
 namespace {
-
-constexpr int ilog2(int b) { return b <= 1 ? 0 : 1 + ilog2(b / 2); }
-
-template <int B>
-struct Log2 {
-    static_assert(B > 0 && (B & (B - 1)) == 0, "power of two");
-    static constexpr int value = ilog2(B);
-};
 
 template <typename T>
 __device__ __forceinline__ T sel4(int p, T c0, T c1, T c2, T c3) {
@@ -47,7 +40,6 @@ __device__ __forceinline__ T sel4(int p, T c0, T c1, T c2, T c3) {
     return (p & 2) ? hi : lo;
 }
 
-__device__ __forceinline__ int wave_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 
 // largest k in [0, n) with h_tile[k] <= tile (h_tile ascending)
@@ -91,89 +83,6 @@ __device__ __forceinline__ uint64_t unrank_row(const BasisDev& b, int64_t row) {
     if (b.sector == 0) return uint64_t(row);
     const int64_t k = find_high_row(b.h_row, b.n_high, row);
     return (b.h_val[k] << b.b_lo) | uint64_t(b.lows[b.h_lobase[k] + (row - b.h_row[k])]);
-}
-
-// ---- lane share of an interleaved row.  A row of nvec vectors is split
-// over LPR lanes in chunks of CB = min(16, lane bytes) bytes, dealt
-// round-robin: lane `sub` owns chunks sub, sub + LPR, sub + 2 LPR, ...  One
-// 16-byte load instruction of the LPR lanes of a row therefore reads
-// LPR * 16 contiguous bytes of it (a whole 128-byte line at LPR = 8), so
-// no line is requested by several instructions.
-template <typename S, int NE, int LPR>
-struct LaneLayout {
-    static constexpr int LB = NE * int(sizeof(S));     // bytes per lane per row
-    static constexpr int CB = LB >= 16 ? 16 : LB;      // chunk bytes
-    static constexpr int NCH = LB / CB;                // chunks per lane
-    static constexpr int CPS = CB / int(sizeof(S));    // scalars per chunk
-    static constexpr int RB = LB * LPR;                // row bytes
-};
-
-template <int CB>
-__device__ __forceinline__ void copy_chunk(char* dst, const char* src) {
-    if constexpr (CB == 16) {
-        const uint4 w = *reinterpret_cast<const uint4*>(src);
-        __builtin_memcpy(dst, &w, 16);
-    } else if constexpr (CB == 8) {
-        const uint2 w = *reinterpret_cast<const uint2*>(src);
-        __builtin_memcpy(dst, &w, 8);
-    } else {
-        static_assert(CB == 4, "chunk of 4, 8 or 16 bytes");
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(src);
-        __builtin_memcpy(dst, &w, 4);
-    }
-}
-
-template <int CB>
-__device__ __forceinline__ void put_chunk(char* dst, const char* src) {
-    if constexpr (CB == 16) {
-        uint4 w;
-        __builtin_memcpy(&w, src, 16);
-        *reinterpret_cast<uint4*>(dst) = w;
-    } else if constexpr (CB == 8) {
-        uint2 w;
-        __builtin_memcpy(&w, src, 8);
-        *reinterpret_cast<uint2*>(dst) = w;
-    } else {
-        uint32_t w;
-        __builtin_memcpy(&w, src, 4);
-        *reinterpret_cast<uint32_t*>(dst) = w;
-    }
-}
-
-// streaming variants: non-temporal hint (data not reused, should not evict
-// the L2 window of the gathers)
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-template <int CB>
-__device__ __forceinline__ void copy_chunk_nt(char* dst, const char* src) {
-    if constexpr (CB == 16) {
-        const u32x4_t w = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(src));
-        __builtin_memcpy(dst, &w, 16);
-    } else if constexpr (CB == 8) {
-        const u32x2_t w = __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(src));
-        __builtin_memcpy(dst, &w, 8);
-    } else {
-        const uint32_t w = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(src));
-        __builtin_memcpy(dst, &w, 4);
-    }
-}
-
-template <int CB>
-__device__ __forceinline__ void put_chunk_nt(char* dst, const char* src) {
-    if constexpr (CB == 16) {
-        u32x4_t w;
-        __builtin_memcpy(&w, src, 16);
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4_t*>(dst));
-    } else if constexpr (CB == 8) {
-        u32x2_t w;
-        __builtin_memcpy(&w, src, 8);
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x2_t*>(dst));
-    } else {
-        uint32_t w;
-        __builtin_memcpy(&w, src, 4);
-        __builtin_nontemporal_store(w, reinterpret_cast<uint32_t*>(dst));
-    }
 }
 
 template <typename S, int NE, int LPR>
@@ -242,38 +151,10 @@ __device__ __forceinline__ void tile_get(const char* tb, int r, int sub, S (&out
         copy_chunk<Ly::CB>(reinterpret_cast<char*>(out) + j * Ly::CB, tb + tile_chunk<S, NE, LPR>(r, j * LPR + sub));
 }
 
-template <typename S, int NE, int LPR>
-__device__ __forceinline__ void load_lane(const S* __restrict__ base, int64_t row, int sub, S (&out)[NE]) {
-    using Ly = LaneLayout<S, NE, LPR>;
-    const char* p = reinterpret_cast<const char*>(base) + row * Ly::RB + sub * Ly::CB;
-#pragma unroll
-    for (int j = 0; j < Ly::NCH; ++j)
-        copy_chunk<Ly::CB>(reinterpret_cast<char*>(out) + j * Ly::CB, p + j * LPR * Ly::CB);
-}
-
-template <typename S, int NE, int LPR>
-__device__ __forceinline__ void store_lane(S* __restrict__ base, int64_t row, int sub, const S (&in)[NE]) {
-    using Ly = LaneLayout<S, NE, LPR>;
-    char* p = reinterpret_cast<char*>(base) + row * Ly::RB + sub * Ly::CB;
-#pragma unroll
-    for (int j = 0; j < Ly::NCH; ++j)
-        put_chunk<Ly::CB>(p + j * LPR * Ly::CB, reinterpret_cast<const char*>(in) + j * Ly::CB);
-}
-
 // A row of zeros in device memory (the widest row: 16 complex128 values).
 // In the windowed and block-staged kernels, lanes whose element is zero read
 // it instead of a partner row, so the accumulation adds exact zeros.
 __device__ __align__(256) uint32_t kZeroRow[64] = {};
-
-// the lane's share of the row at byte address rowp
-template <typename S, int NE, int LPR>
-__device__ __forceinline__ void load_lane_at(const char* rowp, int sub, S (&out)[NE]) {
-    using Ly = LaneLayout<S, NE, LPR>;
-    const char* p = rowp + sub * Ly::CB;
-#pragma unroll
-    for (int j = 0; j < Ly::NCH; ++j)
-        copy_chunk<Ly::CB>(reinterpret_cast<char*>(out) + j * Ly::CB, p + j * LPR * Ly::CB);
-}
 
 // row `idx` of v for an active lane, the zero row otherwise
 template <typename S, int NE, int LPR>
@@ -407,40 +288,6 @@ __device__ __forceinline__ uint32_t parity_masked(typename StateT<W64>::type s, 
     } else {
         return uint32_t(__popc(s & uint32_t(m))) & 1u;
     }
-}
-
-// branch-free choice between two values by a lane mask (all ones / zero):
-// a bitwise select, so no register array is ever indexed per lane
-__device__ __forceinline__ double pick(uint32_t m, double a, double b) {
-    const uint64_t mm = (uint64_t(m) << 32) | m;
-    const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-    return __longlong_as_double(static_cast<long long>((ua & mm) | (ub & ~mm)));
-}
-
-// Reduce one quantity over the rows held by a wavefront.  Each lane holds
-// VPL per-row values (its share of the vectors); afterwards lane L holds the
-// wave sum for the local vector L >> (6 - log2 VPL) of share L & (LPR-1)
-// (vec_lane maps a vector to its share and local index).  Every step is
-// FP64.
-template <typename R, int VPL, int LPR>
-__device__ __forceinline__ double wave_reduce_rows(R (&x)[VPL], int lane) {
-    constexpr int LOGV = Log2<VPL>::value;
-#pragma unroll
-    for (int j = 0; j < LOGV; ++j) {
-        const int half = (VPL >> j) >> 1, off = 32 >> j;
-        const uint32_t up = (lane & off) ? 0xffffffffu : 0u;
-#pragma unroll
-        for (int i = 0; i < half; ++i) {
-            const R lo = x[i], hi = x[i + half];
-            const R send = pick(up, lo, hi);
-            const R keep = pick(up, hi, lo);
-            x[i] = keep + __shfl_xor(send, off, 64);
-        }
-    }
-    double r = double(x[0]);
-#pragma unroll
-    for (int off = 32 >> LOGV; off >= LPR; off >>= 1) r += __shfl_xor(r, off, 64);
-    return r;
 }
 
 // The four per-row FP64 products (|x|^2, Re x*h, |h|^2, |u|^2) of this
@@ -2155,7 +2002,7 @@ __global__ __launch_bounds__(256) void reduce_lz_after_update_multi_kernel(const
 
 // the product's sums (and, for one Lanczos recurrence, the scalar step that
 // reads them)
-static int launch_product_reduce(const hphi_ham* H, int n_parts, int B, const HvLaunch& L, hipStream_t st) {
+int launch_product_reduce(const hphi_ham* H, int n_parts, int B, const HvLaunch& L, hipStream_t st) {
     if (L.lz_sc) {
         if (B != 1) return set_error(HPHI_EINVAL, "Lanczos step fused with the reduction needs one vector");
         reduce_lz_after_hv_kernel<<<1, 256, 0, st>>>(H->d_partials, n_parts, L.reduce_out, H->d_flag, L.lz_sc,
@@ -2543,6 +2390,8 @@ static int launch_hv_s2(const HvLaunch& L, hipStream_t st) {
     const Schedule sc = L.sched ? *L.sched : schedule_for(L.ham, L.nvec, L.dtype);
     const int w = try_launch_hvw<S, CPLX, CCOEF, EX>(L, sc, st);
     if (w != 1) return w;
+    const int gr = try_launch_hvg(L, sc, st);
+    if (gr != 1) return gr;
     if constexpr (!EX) {
         const int b = try_launch_hvs<S, CPLX, CCOEF>(L, sc, st);
         if (b != 1) return b;
@@ -2832,6 +2681,7 @@ static int hv_multi_s(const MultiPlan& P, hipStream_t st) {
 }
 
 static int hv_multi_product(const MultiPlan& P, hipStream_t st) {
+    if (P.group_k) return group_multi_launch(P, st);
     switch (P.dtype) {
         case HPHI_F64: return hv_multi_s<double, false, false>(P, st);
         case HPHI_F32: return hv_multi_s<float, false, false>(P, st);
@@ -2851,6 +2701,36 @@ int hv_multi_launch(const MultiPlan& P, const LzMulti* lz, hipStream_t st) {
     return check_hip(hipGetLastError(), "reduce_multi launch");
 }
 
+std::vector<int> deal_blocks(const std::vector<int64_t>& items, int64_t groups_in) {
+    const int n = int(items.size());
+    const int64_t groups = std::max<int64_t>(n, groups_in);
+    int64_t total = 0;
+    for (int64_t t : items) total += t;
+    std::vector<int64_t> units(n, 1), cap(n);
+    std::vector<double> frac(n, 0.0);
+    int64_t left = groups - n;
+    for (int p = 0; p < n; ++p) {
+        const int64_t t = items[p];
+        cap[p] = std::max<int64_t>(1, ((t + kWavesPerBlock - 1) / kWavesPerBlock + 7) / 8);
+        const double share = total > 0 ? double(groups - n) * double(t) / double(total) : 0.0;
+        const int64_t whole = std::min<int64_t>(int64_t(share), cap[p] - 1);
+        units[p] += whole;
+        frac[p] = share - double(int64_t(share));
+        left -= whole;
+    }
+    std::vector<int> order(n);
+    for (int p = 0; p < n; ++p) order[p] = p;
+    std::sort(order.begin(), order.end(), [&](int a, int b) { return frac[a] > frac[b] || (frac[a] == frac[b] && a < b); });
+    for (int k = 0; k < n && left > 0; ++k)
+        if (units[order[k]] < cap[order[k]]) {
+            ++units[order[k]];
+            --left;
+        }
+    std::vector<int> begin(n + 1, 0);
+    for (int p = 0; p < n; ++p) begin[p + 1] = begin[p] + int(units[p] * 8);
+    return begin;
+}
+
 int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     if (n < 1 || !out) return set_error(HPHI_EINVAL, "hv_multi_prepare: no problems");
     MultiPlan P;
@@ -2860,7 +2740,6 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     P.sector = Ls[0].ham->basis->dev.sector != 0;
     P.w64 = Ls[0].ham->basis->nbits > 32;
     size_t lds = 0;
-    int64_t tiles_total = 0;
     for (int p = 0; p < n; ++p) {
         const HvLaunch& L = Ls[p];
         if (L.nvec != 1 || L.dtype != P.dtype || L.ham->is_complex != P.cc ||
@@ -2868,7 +2747,10 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
             return set_error(HPHI_EINVAL, "hv_multi_prepare: problems differ in dtype, coefficients or space kind");
         const size_t b = hv_stage_bytes(L.ham, P.sector);
         if (b > lds) lds = b;
-        tiles_total += L.ham->basis->dev.n_tiles;
+    }
+    {
+        const int rc = group_multi_prepare(Ls, n, out);
+        if (rc != 1) return rc;
     }
     const Schedule sc = schedule_for(Ls[0].ham, 1, P.dtype);
     P.gtab = P.w64 || !sc.stage_tables || lds > kLdsStageBytes;
@@ -2887,29 +2769,9 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     if (occ < 1) occ = 1;
     int per_cu = occupancy_with_lds(occ, P.lds);
     if (sc.blocks_per_cu > 0 && sc.blocks_per_cu < per_cu) per_cu = sc.blocks_per_cu;
-    const int64_t groups = std::max<int64_t>(n, int64_t(per_cu) * cu_count() / 8);
-    std::vector<int64_t> units(n, 1), cap(n);
-    std::vector<double> frac(n, 0.0);
-    int64_t left = groups - n;
-    for (int p = 0; p < n; ++p) {
-        const int64_t t = Ls[p].ham->basis->dev.n_tiles;
-        cap[p] = std::max<int64_t>(1, ((t + kWavesPerBlock - 1) / kWavesPerBlock + 7) / 8);
-        const double share = tiles_total > 0 ? double(groups - n) * double(t) / double(tiles_total) : 0.0;
-        const int64_t whole = std::min<int64_t>(int64_t(share), cap[p] - 1);
-        units[p] += whole;
-        frac[p] = share - double(int64_t(share));
-        left -= whole;
-    }
-    std::vector<int> order(n);
-    for (int p = 0; p < n; ++p) order[p] = p;
-    std::sort(order.begin(), order.end(), [&](int a, int b) { return frac[a] > frac[b] || (frac[a] == frac[b] && a < b); });
-    for (int k = 0; k < n && left > 0; ++k)
-        if (units[order[k]] < cap[order[k]]) {
-            ++units[order[k]];
-            --left;
-        }
-    std::vector<int> begin(n + 1, 0);
-    for (int p = 0; p < n; ++p) begin[p + 1] = begin[p] + int(units[p] * 8);
+    std::vector<int64_t> work(n);
+    for (int p = 0; p < n; ++p) work[p] = Ls[p].ham->basis->dev.n_tiles;
+    const std::vector<int> begin = deal_blocks(work, int64_t(per_cu) * cu_count() / 8);
     P.grid = begin[n];
     // device memory: args | begin | partials | reductions
     const size_t a_bytes = size_t(n) * sizeof(HvArgs);

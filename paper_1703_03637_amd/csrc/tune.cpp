@@ -146,7 +146,7 @@ extern "C" int hphi_hv_tune(const hphi_ham* ham, const void* v, void* u, int64_t
     for (int bpc : (wide_sector ? std::vector<int>{0, 4, 6} : std::vector<int>{0, 4})) {
         for (int lpr : lprs) {
             Schedule s;
-            s.sector_blocks = 0;
+            s.sector_blocks = 0;   // the per-tile kernel; the class-blocked one is a candidate of its own
             s.lpr = lpr;
             s.blocks_per_cu = bpc;
             s.windowed = 0;
@@ -177,6 +177,14 @@ extern "C" int hphi_hv_tune(const hphi_ham* ham, const void* v, void* u, int64_t
             s.nt_streams = 0;
         }
     }
+    if (ham->grp)
+        for (int bpc : {0, 2, 3}) {
+            Schedule s;
+            s.windowed = 0;
+            s.sector_blocks = 2;
+            s.blocks_per_cu = bpc;
+            cands.push_back(s);
+        }
     if (blockable)
         for (int bpc : {1, 2, 3}) {
             Schedule s;
