@@ -26,15 +26,36 @@ int env_int(const char* name, int dflt) {
     return (e && *e) ? atoi(e) : dflt;
 }
 
-Schedule default_schedule(const hphi_basis* B, int nvec) {
+// Full space (microseconds per product on the Kitaev-Heisenberg honeycomb,
+// before -> after this rule replaced 3 passes of 2 MB windows everywhere):
+//   rows of at most 16 bytes: one pass in natural order with four blocks per
+//     CU.  A lane holds a whole row, so a wavefront's partner rows are whole
+//     lines, and a second pass costs more than the L2 misses it saves; more
+//     rows in flight would leave the L2 (complex128, 24 sites 911 -> 627, 805
+//     with all blocks; 26 sites 3652 -> 2745; FP32, 24 sites 720 -> 522).
+//   wider rows: one windowed pass while the vector stays in the memory-side
+//     cache (64 bytes: up to 256 MB, 22 sites 662 -> 559; 128 bytes, whose
+//     window passes pay sooner: up to 32 MB, 18 sites 81 -> 75), else two
+//     passes of 1 MB windows (complex64 x 16, 24 sites 6181 -> 4896; x 4, 1393
+//     -> 1314).  Rows of 256 bytes keep three passes of 2 MB (24 sites 14970
+//     against 14697, 20 sites 517 against 567).
+Schedule default_schedule(const hphi_basis* B, int nvec, int dtype) {
     Schedule s;
     s.windowed = 1;
     s.window_kb = 2048;
     s.max_passes = 3;
+    const size_t row = size_t(nvec) * dtype_size(dtype);
+    const size_t bytes = row * size_t(B->dim);
+    const bool full = B->dev.sector == 0;
+    if (full && (row <= 16 || bytes <= (size_t(row <= 64 ? 256 : 32) << 20))) s.max_passes = 1;
+    else if (full && row <= 128) {
+        s.window_kb = 1024;
+        s.max_passes = 2;
+    }
     s.lpr = nvec >= 16 ? 4 : (nvec >= 8 ? 2 : 1);
     // sectors wider than 32 bits: 6 resident blocks per CU measured fastest
     // (more waves in flight thrash the L2 on the 36-bit kagome sector)
-    s.blocks_per_cu = (B->dev.sector != 0 && B->nbits > 32) ? 6 : 0;
+    s.blocks_per_cu = (B->dev.sector != 0 && B->nbits > 32) ? 6 : (full && row <= 16) ? 4 : 0;
     s.nt_streams = nvec >= 8 ? 1 : 0;
     // overrides for experiments
     s.windowed = env_int("HPHI_WINDOWED", s.windowed);
@@ -110,7 +131,7 @@ Schedule schedule_for(const hphi_ham* ham, int nvec, int dtype) {
         for (const auto& t : H->tuned)
             if (t.nvec == nvec && t.dtype == dtype) return t.s;
     }
-    Schedule s = default_schedule(H->basis, nvec);
+    Schedule s = default_schedule(H->basis, nvec, dtype);
     if (getenv("HPHI_TUNE_CACHE")) {
         Schedule c;
         if (cache_lookup(signature(H, nvec, dtype), c)) s = c;
