@@ -106,6 +106,12 @@ int replay_pairs(hipStream_t st, Body body, int reps, const char* what = nullptr
     return rc;
 }
 
+// the product's sums into `out` (device; nullptr: none)
+static void set_sums(HvLaunch& L, double* out) {
+    L.tail.mode = out ? kTailSums : kTailNone;
+    L.tail.out = out;
+}
+
 static bool valid_dtype(int dt) { return dt == HPHI_F64 || dt == HPHI_C128 || dt == HPHI_F32 || dt == HPHI_C64; }
 static bool valid_nvec(int64_t n) { return n == 1 || n == 2 || n == 4 || n == 8 || n == 16; }
 
@@ -139,7 +145,7 @@ extern "C" int hphi_hv(const hphi_ham* ham, const void* v, void* u, int64_t nvec
     L.nvec = int(nvec);
     L.dtype = dtype;
     L.stop = nullptr;
-    L.reduce_out = o.reduce;
+    set_sums(L, o.reduce);
     return launch_hv(L, (hipStream_t)stream);
 }
 
@@ -166,7 +172,7 @@ extern "C" int hphi_hv_cma(const hphi_ham* ham, const void* v, void* u, int64_t 
     L.b = o.b;
     L.nvec = int(nvec);
     L.dtype = dtype;
-    L.reduce_out = o.reduce;
+    set_sums(L, o.reduce);
     return launch_hv_cma(L, P, (hipStream_t)stream);
 }
 
@@ -252,11 +258,10 @@ extern "C" int hphi_expect(const hphi_ham* obs, const void* psi, int64_t nvec, i
     L.b = 0.0;
     L.nvec = int(nvec);
     L.dtype = dtype;
-    L.reduce_out = obs->d_red;
-    hipStream_t st = (hipStream_t)stream;
-    int rc = launch_hv(L, st);
-    if (rc) return rc;
-    return launch_expect(obs->d_red, out, int(nvec), st);
+    set_sums(L, obs->d_red);
+    L.tail.mode = kTailExpect;
+    L.tail.obs = out;
+    return launch_hv(L, (hipStream_t)stream);
 }
 
 extern "C" int hphi_tpq_step(const hphi_ham* ham, const void* psi_in, void* psi_out, int64_t nvec, int32_t dtype,
@@ -278,11 +283,13 @@ extern "C" int hphi_tpq_step(const hphi_ham* ham, const void* psi_in, void* psi_
     L.b = l;
     L.nvec = int(nvec);
     L.dtype = dtype;
-    L.reduce_out = ham->d_red;
-    hipStream_t st = (hipStream_t)stream;
-    int rc = launch_hv(L, st);
-    if (rc) return rc;
-    return launch_tpq_obs(ham->d_red, obs, int(nvec), ns, l, k, st);
+    set_sums(L, ham->d_red);
+    L.tail.mode = kTailTpq;
+    L.tail.obs = obs;
+    L.tail.ns = ns;
+    L.tail.l = l;
+    L.tail.k = k;
+    return launch_hv(L, (hipStream_t)stream);
 }
 
 extern "C" int hphi_tpq_run(const hphi_ham* ham, void* psi_a, void* psi_b, int64_t nvec, int32_t dtype, double l,
@@ -313,9 +320,13 @@ extern "C" int hphi_tpq_run(const hphi_ham* ham, void* psi_a, void* psi_b, int64
         L.b = l;
         L.nvec = int(nvec);
         L.dtype = dtype;
-        L.reduce_out = ham->d_red;
-        int rc = launch_hv(L, s);
-        return rc ? rc : launch_tpq_obs_run(ham->d_red, S, obs_log, int(nvec), ns, l, s);
+        set_sums(L, ham->d_red);
+        L.tail.mode = kTailTpqRun;
+        L.tail.obs = obs_log;
+        L.tail.run = S;
+        L.tail.ns = ns;
+        L.tail.l = l;
+        return launch_hv(L, s);
     };
     int rc = launch_tpq_run_init(S, k0, st);
     if (!rc) rc = step(0, true, st);      // eager: allocates lazily built plans before any capture
@@ -363,10 +374,14 @@ extern "C" int hphi_tpq_run_noalloc(const hphi_ham* ham, void* psi_a, void* psi_
         L.b = l;
         L.nvec = int(nvec);
         L.dtype = dtype;
-        L.reduce_out = ham->d_red;
+        set_sums(L, ham->d_red);
+        L.tail.mode = kTailTpqRun;
+        L.tail.obs = obs_log;
+        L.tail.run = S;
+        L.tail.ns = ns;
+        L.tail.l = l;
         L.no_alloc = true;
         rc = launch_hv(L, st);
-        if (!rc) rc = launch_tpq_obs_run(ham->d_red, S, obs_log, int(nvec), ns, l, st);
     }
     return rc;
 }
@@ -382,16 +397,20 @@ struct LzDev {
     double* evec = nullptr;
     double* red = nullptr;
     double* spart = nullptr;   // partials of the streaming kernels
+    uint32_t* tickets = nullptr;   // [2][kTickets] of the product and of the update
     void* mem = nullptr;
 };
 
 constexpr int kStreamGrid = 1024;
 
 int lz_alloc(LzDev& D, int n) {
-    const size_t bytes = 256 + 3 * size_t(n) * 8 + 64 * 8 + size_t(kStreamGrid) * 8 + 1024;
+    const size_t tick = size_t(2) * kTickets * 4;
+    const size_t bytes = tick + 256 + 3 * size_t(n) * 8 + 64 * 8 + size_t(kStreamGrid) * 8 + 1024;
     char* p = nullptr;
     if (int rc = dev_alloc((void**)&p, bytes, "hphi_lanczos: scalar workspace")) return rc;
     D.mem = p;
+    D.tickets = (uint32_t*)p;
+    p += tick;
     D.sc = (LzScalars*)p;
     p += 256;
     D.alpha = (double*)p;
@@ -429,15 +448,17 @@ int lz_iteration(const hphi_ham* H, int dtype, void* X, void* Y, bool first, LzD
     L.nvec = 1;
     L.dtype = dtype;
     L.stop = stop;
-    L.reduce_out = D.red;
-    // each reduction launch also takes the scalar step that reads its sums
-    L.lz_sc = D.sc;
-    L.lz_alpha = D.alpha;
-    L.lz_evec = acc ? D.evec : nullptr;
+    // the product's last block also takes alpha_k, the update's last block beta
+    set_sums(L, D.red);
+    L.tail.mode = kTailLanczos;
+    L.tail.tickets = D.tickets;
+    L.tail.sc = D.sc;
+    L.tail.alpha = D.alpha;
+    L.tail.evec = acc ? D.evec : nullptr;
     int rc = launch_hv(L, st);
     if (rc) return rc;
-    return launch_lanczos_update_lz(Y, X, H->basis->dim, dtype, D.sc, acc, D.spart, grid, D.red, D.beta, D.alpha,
-                                    H->d_flag, st);
+    return launch_lanczos_update_lz(Y, X, H->basis->dim, dtype, D.sc, acc, D.spart, grid, D.beta, D.alpha,
+                                    H->d_flag, D.tickets + kTickets, st);
 }
 
 // Run the recurrence from v0 for n_max steps (pass 1 or the eigenvector pass).
@@ -446,7 +467,8 @@ int lz_run(const hphi_ham* H, int dtype, const void* v0, void* A, void* B, LzDev
     const int64_t dim = H->basis->dim;
     const int64_t scalars = dim * (dtype_complex(dtype) ? 2 : 1);
     const int grid = stream_grid_for(scalars);
-    int rc = launch_copy_norm(v0, A, dim, dtype, D.spart, grid, D.red, H->d_flag, st);
+    int rc = launch_fill_zero(D.tickets, int64_t(2) * kTickets * 4, st);
+    if (!rc) rc = launch_copy_norm(v0, A, dim, dtype, D.spart, grid, D.red, H->d_flag, st);
     if (rc) return rc;
     // the eigenvector accumulator starts at zero; it may share v0's buffer,
     // which is not read again after the copy above
@@ -489,16 +511,20 @@ struct LzBatch {
     double* evec = nullptr;
     double* red = nullptr;     // [n][kNQ]
     double* spart = nullptr;   // [kStreamGrid]
+    uint32_t* tickets = nullptr;   // [n][2][kTickets] of the product and of the update
     void* mem = nullptr;
 };
 
 int lzb_alloc(LzBatch& D, int n, int n_iter) {
     const size_t sc_b = (size_t(n) * sizeof(LzScalars) + 255) / 256 * 256;
     const size_t arr = size_t(n) * n_iter * 8;
-    const size_t bytes = sc_b + 3 * arr + size_t(n) * kNQ * 8 + size_t(kStreamGrid) * 8 + 1024;
+    const size_t tick = size_t(n) * 2 * kTickets * 4;
+    const size_t bytes = tick + sc_b + 3 * arr + size_t(n) * kNQ * 8 + size_t(kStreamGrid) * 8 + 1024;
     char* p = nullptr;
     if (int rc = dev_alloc((void**)&p, bytes, "hphi_lanczos: batched workspace")) return rc;
     D.mem = p;
+    D.tickets = (uint32_t*)p;
+    p += tick;
     D.sc = (LzScalars*)p;
     p += sc_b;
     D.alpha = (double*)p;
@@ -525,10 +551,9 @@ struct BatchPlans {
 
 // parity 0: X = A, Y = B; parity 1: X = B, Y = A
 int lzb_plans(const hphi_ham* const* H, int n, int dtype, void* const* A, void* const* Bv, LzBatch& D,
-              void* const* acc, BatchPlans& P) {
+              void* const* acc, int n_iter, BatchPlans& P) {
     std::vector<HvLaunch> Ls(n);
     std::vector<UpdDesc> U(n);
-    std::vector<double*> ured(n);
     for (int first = 1; first >= 0; --first)
         for (int q = 0; q < (first ? 1 : 2); ++q) {
             for (int p = 0; p < n; ++p) {
@@ -547,7 +572,12 @@ int lzb_plans(const hphi_ham* const* H, int n, int dtype, void* const* A, void* 
                 L.nvec = 1;
                 L.dtype = dtype;
                 L.stop = &D.sc[p].stop;
-                L.reduce_out = D.red + size_t(kNQ) * p;
+                set_sums(L, D.red + size_t(kNQ) * p);
+                L.tail.mode = kTailLanczos;
+                L.tail.tickets = D.tickets + size_t(2 * p) * kTickets;
+                L.tail.sc = D.sc + p;
+                L.tail.alpha = D.alpha + size_t(n_iter) * p;
+                L.tail.evec = acc ? D.evec + size_t(n_iter) * p : nullptr;
                 if (!first) {
                     UpdDesc& u = U[p];
                     u = UpdDesc{};
@@ -559,22 +589,22 @@ int lzb_plans(const hphi_ham* const* H, int n, int dtype, void* const* A, void* 
                     u.ec = &D.sc[p].ecoef;
                     u.stop = &D.sc[p].stop;
                     u.flag = H[p]->d_flag;
-                    ured[p] = D.red + size_t(kNQ) * p;
+                    u.sc = D.sc + p;
+                    u.tickets = D.tickets + size_t(2 * p + 1) * kTickets;
+                    u.beta = D.beta + size_t(n_iter) * p;
+                    u.alpha = D.alpha + size_t(n_iter) * p;
                 }
             }
             int rc = hv_multi_prepare(Ls.data(), n, first ? &P.hv_first : &P.hv[q]);
-            if (!rc && !first) rc = upd_multi_prepare(U.data(), ured.data(), n, dtype, &P.upd[q]);
+            if (!rc && !first) rc = upd_multi_prepare(U.data(), n, dtype, &P.upd[q]);
             if (rc) return rc;
         }
     return HPHI_OK;
 }
 
-int lzb_iteration(const BatchPlans& P, int parity, bool first, LzBatch& D, bool acc, int n_iter, hipStream_t st) {
-    // each reduction launch also takes the scalar steps that read its sums
-    const LzMulti lz{D.sc, D.alpha, D.beta, acc ? D.evec : nullptr, n_iter};
-    int rc = hv_multi_launch(first ? P.hv_first : P.hv[parity], &lz, st);
-    if (!rc) rc = upd_multi_launch(P.upd[parity], &lz, st);
-    return rc;
+int lzb_iteration(const BatchPlans& P, int parity, bool first, hipStream_t st) {
+    const int rc = hv_multi_launch(first ? P.hv_first : P.hv[parity], st);
+    return rc ? rc : upd_multi_launch(P.upd[parity], st);
 }
 
 // Run all recurrences from v0 for up to n_max[p] steps (pass 1, or the
@@ -582,6 +612,7 @@ int lzb_iteration(const BatchPlans& P, int parity, bool first, LzBatch& D, bool 
 int lzb_run(const hphi_ham* const* H, int n, int dtype, const void* const* v0, void* const* A, void* const* Bv,
             LzBatch& D, const int* n_max, double tol, void* const* acc, bool use_graph, int n_iter, hipStream_t st) {
     int N = 0;
+    if (int rc = launch_fill_zero(D.tickets, int64_t(n) * 2 * kTickets * 4, st)) return rc;
     for (int p = 0; p < n; ++p) {
         const int64_t dim = H[p]->basis->dim;
         const int grid = stream_grid_for(dim * (dtype_complex(dtype) ? 2 : 1));
@@ -594,8 +625,8 @@ int lzb_run(const hphi_ham* const* H, int n, int dtype, const void* const* v0, v
         if (n_max[p] > N) N = n_max[p];
     }
     BatchPlans P;
-    int rc = lzb_plans(H, n, dtype, A, Bv, D, acc, P);
-    if (!rc) rc = lzb_iteration(P, 0, true, D, acc != nullptr, n_iter, st);
+    int rc = lzb_plans(H, n, dtype, A, Bv, D, acc, n_iter, P);
+    if (!rc) rc = lzb_iteration(P, 0, true, st);
     int k = 1;
     if (!rc && use_graph && N >= 3) {
         hipStream_t cs;
@@ -609,8 +640,8 @@ int lzb_run(const hphi_ham* const* H, int n, int dtype, const void* const* v0, v
             hipGraphExec_t ge = nullptr;
             rc = check_hip(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "begin capture");
             if (!rc) {
-                int r1 = lzb_iteration(P, 1, false, D, acc != nullptr, n_iter, cs);
-                int r2 = r1 ? r1 : lzb_iteration(P, 0, false, D, acc != nullptr, n_iter, cs);
+                int r1 = lzb_iteration(P, 1, false, cs);
+                int r2 = r1 ? r1 : lzb_iteration(P, 0, false, cs);
                 hipError_t e = hipStreamEndCapture(cs, &g);
                 rc = r2 ? r2 : check_hip(e, "end capture");
             }
@@ -625,7 +656,7 @@ int lzb_run(const hphi_ham* const* H, int n, int dtype, const void* const* v0, v
             (void)hipEventDestroy(ev);
         }
     }
-    for (; !rc && k < N; ++k) rc = lzb_iteration(P, k & 1, false, D, acc != nullptr, n_iter, st);
+    for (; !rc && k < N; ++k) rc = lzb_iteration(P, k & 1, false, st);
     // plans are read by kernels still in flight: release after the stream drains
     hipError_t e = hipStreamSynchronize(st);
     P.release();
@@ -644,7 +675,7 @@ int refine_one(const hphi_ham* H, const void* x, int x_dtype, double* red, hphi_
     L.b = 0.0;
     L.nvec = 1;
     L.dtype = x_dtype;
-    L.reduce_out = red;
+    set_sums(L, red);
     int rc = launch_hv(L, st);
     double q[4];
     if (!rc) rc = check_hip(hipMemcpyAsync(q, red, 32, hipMemcpyDeviceToHost, st), "copy red");
@@ -872,7 +903,7 @@ extern "C" int hphi_cg_refine(const hphi_ham* ham, void* x, int32_t dtype, doubl
         L.b = -Ep;
         L.nvec = 1;
         L.dtype = dtype;
-        L.reduce_out = red;
+        set_sums(L, red);
         int r = launch_hv(L, st);
         double q[2];
         if (!r) r = host(q, red, 2);

@@ -168,6 +168,7 @@ struct HvgArgs {
     double a, b;
     const int* stop;
     double* partials;
+    Tail tail;
     ExportArgs ex;
 };
 

@@ -10,8 +10,8 @@
 
 namespace hphi {
 
-int launch_hvg_f32(const HvgArgs& A, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
-int launch_hvg_f64(const HvgArgs& A, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
+int launch_hvg_f32(HvgArgs& A, const HvLaunch& L, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
+int launch_hvg_f64(HvgArgs& A, const HvLaunch& L, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
 int launch_hvg_multi_f32(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
                          hipStream_t st);
 int launch_hvg_multi_f64(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
@@ -318,14 +318,18 @@ int group_build(const hphi_basis* B, const GroupBuild& G) {
 }
 
 // High halves per wavefront.  More of them share one decode and put more
-// gathers in flight, but leave fewer wavefronts.
+// gathers in flight, but leave fewer wavefronts: 4,900 rows of 16 complex128
+// vectors take 20 us at K = 1 and 24 at 2, 853,776 complex128 rows (24 Lanczos
+// steps twice) 4.5, 3.8, 3.5 and 3.8 ms at 1, 2, 4 and 8, 20,058,300 FP64 rows
+// 1.03, 0.63, 0.59 and 0.58 ms, 1.25e9 FP32 rows 75, 69, 57 and 36 ms.  Rows of
+// more than two scalars hold K = 4 without spilling registers, not 8.
 static int group_k(int ns, int dtype, int64_t rows) {
     if (const char* e = std::getenv("HPHI_GROUP_K")) {
         const int k = std::atoi(e);
         if (k == 1 || k == 2 || k == 4 || (k == 8 && ns <= 2)) return k;
     }
     if (rows >= (int64_t(1) << 22)) return ns <= 2 ? 8 : 4;
-    return rows >= (int64_t(1) << 19) ? 4 : 2;
+    return rows >= (int64_t(1) << 19) ? 4 : rows >= (int64_t(1) << 15) ? 2 : 1;
 }
 
 static void group_args(const hphi_ham* H, int k, bool cplx, HvgArgs& A) {
@@ -359,13 +363,13 @@ int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
     A.b = L.b;
     A.stop = L.stop;
     A.partials = H->d_partials;
+    A.tail = L.tail;
     if (L.ex) A.ex = *L.ex;
     int grid = 0;
     const bool sign = B->desc.particle == HPHI_FERMION;
-    const int rc = f64 ? launch_hvg_f64(A, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
-                       : launch_hvg_f32(A, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
-    if (rc || L.ex || !L.reduce_out) return rc;
-    return launch_product_reduce(H, grid, L.nvec, L, st);
+    const int rc = f64 ? launch_hvg_f64(A, L, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
+                       : launch_hvg_f32(A, L, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
+    return rc ? rc : launch_product_tail(L, grid, st);
 }
 
 // Several problems that all have the class-blocked tables: the problems share
@@ -381,7 +385,7 @@ int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     P.dtype = dtype;
     int64_t rows = 0;
     for (int p = 0; p < n; ++p) rows += Ls[p].ham->basis->dim;
-    P.group_k = group_k(ns, dtype, rows);
+    P.group_k = std::max(2, group_k(ns, dtype, rows));
     P.cc = false;
     std::vector<HvgArgs> args(n, HvgArgs{});
     std::vector<int64_t> items(n);
@@ -410,19 +414,17 @@ int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     const size_t a_bytes = size_t(n) * sizeof(HvgArgs);
     const size_t b_off = (a_bytes + 255) / 256 * 256;
     const size_t p_off = b_off + (size_t(n + 1) * 4 + 255) / 256 * 256;
-    const size_t r_off = p_off + size_t(P.grid) * kNQ * sizeof(double);
-    const size_t total = r_off + size_t(n) * sizeof(RedDesc);
+    const size_t total = p_off + size_t(P.grid) * kNQ * sizeof(double);
     char* mem = nullptr;
     if (int rc = dev_alloc((void**)&mem, total, "hv_multi_prepare")) return rc;
-    std::vector<RedDesc> red(n);
     double* partials = reinterpret_cast<double*>(mem + p_off);
     for (int p = 0; p < n; ++p) {
         args[p].partials = partials + size_t(begin[p]) * kNQ;
-        red[p] = RedDesc{args[p].partials, begin[p + 1] - begin[p], 0, Ls[p].reduce_out, Ls[p].stop, Ls[p].ham->d_flag};
+        args[p].tail = Ls[p].tail;
+        args[p].tail.flag = Ls[p].ham->d_flag;
     }
     hipError_t e = hipMemcpy(mem, args.data(), a_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(mem + b_off, begin.data(), size_t(n + 1) * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(mem + r_off, red.data(), size_t(n) * sizeof(RedDesc), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(mem);
         return check_hip(e, "hv_multi_prepare: upload");
@@ -430,7 +432,6 @@ int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     P.mem = mem;
     P.d_args = mem;
     P.d_begin = reinterpret_cast<const int*>(mem + b_off);
-    P.d_red = reinterpret_cast<const RedDesc*>(mem + r_off);
     *out = P;
     return HPHI_OK;
 }

@@ -9,6 +9,7 @@
 #include "group.h"
 #include "hphi_internal.h"
 #include "lane.h"
+#include "tail.h"
 
 namespace hphi {
 namespace {
@@ -116,12 +117,14 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
     // advance together
     const int xcd = blk & 7;
     const uint32_t g_begin = A.grp.begin[xcd], g_last = A.grp.begin[xcd + 1] - 1;   // the last one only closes the range
-    const uint32_t i_end = A.grp.items[xcd];
+    const uint32_t i_end = A.grp.items[xcd] * LPR;   // the LPR passes of a tile are neighbouring wavefronts
     const uint32_t i_step = uint32_t(nblk >> 3) * kWavesPerBlock;
 
     double wq[kNQ] = {0.0, 0.0, 0.0, 0.0};
     uint32_t gi = g_begin;
-    for (uint32_t item = uint32_t(blk >> 3) * kWavesPerBlock + uint32_t(wave); item < i_end; item += i_step) {
+    for (uint32_t it = uint32_t(blk >> 3) * kWavesPerBlock + uint32_t(wave); it < i_end; it += i_step) {
+        const uint32_t item = it / LPR;
+        const int pass = int(it % LPR);
         if (item >= groups[gi + 1].item0) {
             // the last group that starts at or before the item
             uint32_t lo = gi + 1, hi_g = g_last - 1;
@@ -135,10 +138,9 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
         const uint32_t p0 = groups[gi].p0, nk = groups[gi].n, ci = groups[gi].cls;
         const uint32_t tile = item - groups[gi].item0;
         const uint32_t n_l = cls[ci].n_l, l_off = cls[ci].l_off;
-#pragma unroll 1
-        for (int pass = 0; pass < LPR; ++pass) {
+        {
             const uint32_t r = tile * 64u + uint32_t(pass * RPW + rlane);
-            if (LPR > 1 && tile * 64u + uint32_t(pass * RPW) >= n_l) break;
+            if (LPR > 1 && tile * 64u + uint32_t(pass * RPW) >= n_l) continue;
             const bool valid = r < n_l;
             const uint32_t rr = valid ? r : n_l - 1;
             const uint32_t li = l_off + rr;
@@ -361,7 +363,11 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
 #pragma unroll
             for (int w = 0; w < kWavesPerBlock; ++w) s += sh[w][qi][L];
         }
-        A.partials[size_t(blk) * size_t(kNQ * B) + threadIdx.x] = s;
+        put_partial(&A.partials[size_t(blk) * size_t(kNQ * B) + threadIdx.x], s);
+    }
+    if (A.tail.mode != kTailNone) {
+        __syncthreads();   // the block sums are read
+        product_tail(*(const Tail*)&A.tail, A.partials, blk, nblk, B, &sh[0][0][0]);
     }
 }
 
@@ -393,13 +399,14 @@ int group_occupancy(Kernel k) {
 }
 
 template <typename S, int NS, int LPR, int K, bool SIGN, bool EX>
-int launch_hvg_k(const HvgArgs& A, int per_cu_cap, int cus, hipStream_t st, int* grid_out) {
+int launch_hvg_k(HvgArgs& A, const HvLaunch& L, int per_cu_cap, int cus, hipStream_t st, int* grid_out) {
     static const int occ = group_occupancy(hvg_kernel<S, NS, LPR, K, SIGN, EX>);
     const int per_cu = per_cu_cap > 0 && per_cu_cap < occ ? per_cu_cap : occ;
     int64_t g = 0;
-    for (int x = 0; x < 8; ++x) g = std::max<int64_t>(g, (int64_t(A.grp.items[x]) + kWavesPerBlock - 1) / kWavesPerBlock);
+    for (int x = 0; x < 8; ++x) g = std::max<int64_t>(g, (int64_t(A.grp.items[x]) * LPR + kWavesPerBlock - 1) / kWavesPerBlock);
     g = std::min<int64_t>(std::max<int64_t>(g, 1) * 8, int64_t(per_cu) * cus / 8 * 8);
     g = std::min<int64_t>(g, kMaxGrid);
+    A.tail = product_tail_of(L, int(g));
     hvg_kernel<S, NS, LPR, K, SIGN, EX><<<int(g), kBlock, 0, st>>>(A);
     *grid_out = int(g);
     return check_hip(hipGetLastError(), "hvg_kernel launch");
@@ -414,29 +421,29 @@ struct GroupLanes {
 };
 
 template <typename S, int NS, bool SIGN, bool EX>
-int launch_hvg_ns(const HvgArgs& A, int k, int cap, int cus, hipStream_t st, int* grid) {
+int launch_hvg_ns(HvgArgs& A, const HvLaunch& L, int k, int cap, int cus, hipStream_t st, int* grid) {
     constexpr int LPR = GroupLanes<S, NS>::value;
     switch (k) {
-        case 1: return launch_hvg_k<S, NS, LPR, 1, SIGN, EX>(A, cap, cus, st, grid);
-        case 2: return launch_hvg_k<S, NS, LPR, 2, SIGN, EX>(A, cap, cus, st, grid);
-        case 4: return launch_hvg_k<S, NS, LPR, 4, SIGN, EX>(A, cap, cus, st, grid);
+        case 1: return launch_hvg_k<S, NS, LPR, 1, SIGN, EX>(A, L, cap, cus, st, grid);
+        case 2: return launch_hvg_k<S, NS, LPR, 2, SIGN, EX>(A, L, cap, cus, st, grid);
+        case 4: return launch_hvg_k<S, NS, LPR, 4, SIGN, EX>(A, L, cap, cus, st, grid);
         case 8:
-            if constexpr (NS / LPR <= 2) return launch_hvg_k<S, NS, LPR, 8, SIGN, EX>(A, cap, cus, st, grid);
+            if constexpr (NS / LPR <= 2) return launch_hvg_k<S, NS, LPR, 8, SIGN, EX>(A, L, cap, cus, st, grid);
             break;
     }
     return set_error(HPHI_EINVAL, "class-blocked product: bad group size %d", k);
 }
 
 template <typename S, bool SIGN, bool EX>
-int launch_hvg_s(const HvgArgs& A, int ns, int k, int cap, int cus, hipStream_t st, int* grid) {
+int launch_hvg_s(HvgArgs& A, const HvLaunch& L, int ns, int k, int cap, int cus, hipStream_t st, int* grid) {
     if constexpr (!EX)
-        if (ns == 1) return launch_hvg_ns<S, 1, SIGN, EX>(A, k, cap, cus, st, grid);
+        if (ns == 1) return launch_hvg_ns<S, 1, SIGN, EX>(A, L, k, cap, cus, st, grid);
     switch (ns) {
-        case 2: return launch_hvg_ns<S, 2, SIGN, EX>(A, k, cap, cus, st, grid);
-        case 4: return launch_hvg_ns<S, 4, SIGN, EX>(A, k, cap, cus, st, grid);
-        case 8: return launch_hvg_ns<S, 8, SIGN, EX>(A, k, cap, cus, st, grid);
-        case 16: return launch_hvg_ns<S, 16, SIGN, EX>(A, k, cap, cus, st, grid);
-        case 32: return launch_hvg_ns<S, 32, SIGN, EX>(A, k, cap, cus, st, grid);
+        case 2: return launch_hvg_ns<S, 2, SIGN, EX>(A, L, k, cap, cus, st, grid);
+        case 4: return launch_hvg_ns<S, 4, SIGN, EX>(A, L, k, cap, cus, st, grid);
+        case 8: return launch_hvg_ns<S, 8, SIGN, EX>(A, L, k, cap, cus, st, grid);
+        case 16: return launch_hvg_ns<S, 16, SIGN, EX>(A, L, k, cap, cus, st, grid);
+        case 32: return launch_hvg_ns<S, 32, SIGN, EX>(A, L, k, cap, cus, st, grid);
     }
     return set_error(HPHI_EINVAL, "class-blocked product: bad row of %d scalars", ns);
 }
@@ -454,10 +461,10 @@ int launch_hvg_multi_k(const HvgArgs* d_args, const int* d_begin, int n, int gri
 
 template <typename S, bool SIGN>
 int launch_hvg_multi_s(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, int grid, int* occ, hipStream_t st) {
-    if (ns == 1) return k == 2 ? launch_hvg_multi_k<S, 1, 2, SIGN>(d_args, d_begin, n, grid, occ, st)
+    if (ns == 1) return k <= 2 ? launch_hvg_multi_k<S, 1, 2, SIGN>(d_args, d_begin, n, grid, occ, st)
                       : k == 4 ? launch_hvg_multi_k<S, 1, 4, SIGN>(d_args, d_begin, n, grid, occ, st)
                                : launch_hvg_multi_k<S, 1, 8, SIGN>(d_args, d_begin, n, grid, occ, st);
-    return k == 2 ? launch_hvg_multi_k<S, 2, 2, SIGN>(d_args, d_begin, n, grid, occ, st)
+    return k <= 2 ? launch_hvg_multi_k<S, 2, 2, SIGN>(d_args, d_begin, n, grid, occ, st)
          : k == 4 ? launch_hvg_multi_k<S, 2, 4, SIGN>(d_args, d_begin, n, grid, occ, st)
                   : launch_hvg_multi_k<S, 2, 8, SIGN>(d_args, d_begin, n, grid, occ, st);
 }
@@ -465,10 +472,10 @@ int launch_hvg_multi_s(const HvgArgs* d_args, const int* d_begin, int n, int ns,
 }  // namespace
 
 #define HVG_INSTANTIATE(S, NAME, MULTI)                                                                                \
-    int NAME(const HvgArgs& A, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g) {           \
-        if (ex) return launch_hvg_s<S, true, true>(A, ns, k, cap, cus, st, g);                                          \
-        return sign ? launch_hvg_s<S, true, false>(A, ns, k, cap, cus, st, g)                                           \
-                    : launch_hvg_s<S, false, false>(A, ns, k, cap, cus, st, g);                                         \
+    int NAME(HvgArgs& A, const HvLaunch& L, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g) {           \
+        if (ex) return launch_hvg_s<S, true, true>(A, L, ns, k, cap, cus, st, g);                                          \
+        return sign ? launch_hvg_s<S, true, false>(A, L, ns, k, cap, cus, st, g)                                           \
+                    : launch_hvg_s<S, false, false>(A, L, ns, k, cap, cus, st, g);                                         \
     }                                                                                                                  \
     int MULTI(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,           \
               hipStream_t st) {                                                                                        \

@@ -333,6 +333,7 @@ extern "C" int hphi_ham_build(const hphi_basis* basis, const hphi_term* terms, i
     const size_t o_part = take(size_t(kMaxGrid) * kNQ * kMaxNvec * sizeof(double));
     const size_t o_up = off;
     const size_t o_red = take(size_t(kNQ) * kMaxNvec * sizeof(double) + 256);
+    const size_t o_tick = take(size_t(kTickets) * 4);
     const size_t o_ops = take(padded.size() * sizeof(DevOp));
     const size_t o_ptab = take(ptab.size() * sizeof(double));
     const size_t base_bytes = off;
@@ -372,10 +373,11 @@ extern "C" int hphi_ham_build(const hphi_basis* basis, const hphi_term* terms, i
     H->d_partials = reinterpret_cast<double*>(m + o_part);
     H->d_red = reinterpret_cast<double*>(m + o_red);
     H->d_flag = reinterpret_cast<int32_t*>(H->d_red + kNQ * kMaxNvec);
+    H->d_tickets = reinterpret_cast<uint32_t*>(m + o_tick);
     H->d_ops = reinterpret_cast<DevOp*>(m + o_ops);
     H->d_ptab = reinterpret_cast<double*>(m + o_ptab);
     const size_t up_bytes = (group ? up_end : base_bytes) - o_up;
-    std::vector<char> up(up_bytes, 0);         // the reductions and the flag start at zero
+    std::vector<char> up(up_bytes, 0);         // the reductions, the flag and the tickets start at zero
     auto fill = [&](size_t at, const void* src, size_t bytes) {
         if (bytes) std::memcpy(up.data() + (at - o_up), src, bytes);
     };

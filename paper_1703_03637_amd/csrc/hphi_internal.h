@@ -210,6 +210,7 @@ struct hphi_ham {
     int grid = 0;                 // persistent grid of the product kernels
     double* d_partials = nullptr; // [kMaxGrid][kNQ * kMaxNvec]
     double* d_red = nullptr;      // [kNQ * kMaxNvec]
+    uint32_t* d_tickets = nullptr; // [kTickets] finished blocks of a product (zero between launches)
     int32_t* d_flag = nullptr;    // sticky non-finite flag word of the reductions (device, one int)
     std::mutex plan_mu;           // guards the lazily built pass plans, staging buffers and tuned schedules
     void* d_stage[2] = {nullptr, nullptr};   // copies of v in a later pass's order (staged schedule)
@@ -257,6 +258,27 @@ struct ExportArgs {
 
 // launch wrappers (kernels.hip)
 struct LzScalars;
+struct TpqRunState;
+// What follows a product's sums: the scalar step of its caller.
+enum { kTailNone = 0, kTailSums, kTailLanczos, kTailTpq, kTailTpqRun, kTailExpect };
+constexpr int kTicketStride = 32;                       // a 128-byte line each
+constexpr int kTickets = (1 + (kMaxGrid + 31) / 32) * kTicketStride;
+struct Tail {
+    int32_t mode = kTailNone;
+    int32_t k = 0;                  // TPQ step index
+    uint32_t* tickets = nullptr;    // [kTickets] count the finished blocks; zero between launches
+    double* out = nullptr;          // [kNQ * nvec] the sums (quantity-major), or null
+    int32_t* flag = nullptr;        // non-finite flag word, or null
+    LzScalars* sc = nullptr;        // Lanczos: alpha_k and the update's coefficients
+    double* alpha = nullptr;
+    const double* evec = nullptr;
+    double* obs = nullptr;          // TPQ observables (of the run: the log), or <O> and <x|x>
+    TpqRunState* run = nullptr;
+    double ns = 0.0, l = 0.0;
+};
+// The last block of the product takes the sums where they are few; more of
+// them are summed faster by a launch of one block per sum.
+constexpr int kTailMax = 16384;
 struct HvLaunch {
     const hphi_ham* ham;
     const void* v;
@@ -268,15 +290,10 @@ struct HvLaunch {
     int nvec;
     int dtype;
     const int* stop;         // device flag: skip all work if nonzero (nullptr = never)
-    double* reduce_out;      // device [kNQ * nvec] or nullptr (quantity-major)
+    Tail tail;               // mode kTailNone: no sums; `tickets` and `flag` are filled in by the launch
     const Schedule* sched;   // nullptr: the tuned or default schedule
     const ExportArgs* ex;    // non-null: element export instead of the product
     bool no_alloc;           // allocate nothing: only plans and staging buffers that exist already
-    // one Lanczos recurrence (nvec 1, stop == &lz_sc->stop): the launch that
-    // reduces the sums also takes the scalar step after the product
-    LzScalars* lz_sc;
-    double* lz_alpha;
-    const double* lz_evec;
 };
 Schedule schedule_for(const hphi_ham* ham, int nvec, int dtype);
 int launch_hv(const HvLaunch& L, hipStream_t st);
@@ -289,21 +306,15 @@ int launch_unrank(const hphi_basis* b, const int64_t* idx, uint64_t* cfg, int64_
 // Lanczos / TPQ support kernels
 int launch_copy_norm(const void* src, void* dst, int64_t n, int dtype, double* partials, int grid,
                      double* red, int32_t* flag, hipStream_t st);
-int launch_lanczos_update(void* y, const void* x, int64_t n, int dtype, const double* c2,
-                          void* acc, const double* ecoef, double* partials, int grid, double* red,
-                          const int* stop, int32_t* flag, hipStream_t st);
-// the same update, with the reduction of |y|^2 and the scalar step after the
-// update (beta, stop test, next scales) in one launch
+// y += c2 x, acc += e x, and in the last block |y|^2 and the scalar step after
+// the update (beta, stop test, next scales)
 int launch_lanczos_update_lz(void* y, const void* x, int64_t n, int dtype, LzScalars* sc, void* acc,
-                             double* partials, int grid, double* red, double* beta, const double* alpha,
-                             int32_t* flag, hipStream_t st);
+                             double* partials, int grid, double* beta, const double* alpha, int32_t* flag,
+                             uint32_t* tickets, hipStream_t st);
 int launch_fill_zero(void* p, int64_t bytes, hipStream_t st);
 // w = a x + b y (FP64, n scalars; w may alias x or y); |w|^2 into *norm2 if non-null
 int launch_lincomb(double* w, const double* x, const double* y, int64_t n, double a, double b, double* partials,
                    double* norm2, hipStream_t st);
-int launch_expect(const double* red, double* out, int nvec, hipStream_t st);
-int launch_tpq_obs(const double* red, double* obs, int nvec, double n_sites, double l, int k,
-                   hipStream_t st);
 // device state of a multi-step TPQ run (hphi_tpq_run): the next step's index
 // k, the step counter j, and the normalizing scales of the last two states
 struct TpqRunState {
@@ -317,8 +328,6 @@ int launch_tpq_run_init(TpqRunState* s, int k0, hipStream_t st);
 // device array of one TpqRunState, its address on the current device
 // (resolved once per device).  Returns an error code or HPHI_OK.
 int tpq_static_state(TpqRunState** out);
-int launch_tpq_obs_run(const double* red, TpqRunState* s, double* obs_log, int nvec, double n_sites, double l,
-                       hipStream_t st);
 
 // per-iteration scalar bookkeeping of the Lanczos recurrence (device, one thread)
 struct LzScalars {
@@ -338,14 +347,6 @@ struct LzScalars {
 int launch_lz_init(LzScalars* sc, const double* red, double tol, int n_max, hipStream_t st);
 
 // ---- several problems per launch (batched Lanczos over uneven sectors)
-struct RedDesc {             // reduce partials[n_parts][nq] into out[nq]
-    const double* partials;
-    int n_parts;
-    int pad;
-    double* out;
-    const int* stop;
-    int32_t* flag;           // non-finite flag word of the problem (or nullptr)
-};
 struct UpdDesc {             // y += c2 x, |y|^2 partials, acc += ec x
     void* y;
     const void* x;
@@ -356,6 +357,10 @@ struct UpdDesc {             // y += c2 x, |y|^2 partials, acc += ec x
     double* partials;        // set by the plan
     const int* stop;
     int32_t* flag;           // non-finite flag word of the problem's Hamiltonian
+    LzScalars* sc;
+    uint32_t* tickets;       // [kTickets]
+    double* beta;
+    const double* alpha;
 };
 // Launch plan of one batched product: per-problem arguments, block ranges
 // (multiples of 8) and reductions, uploaded once and replayed by graphs.
@@ -371,26 +376,19 @@ struct MultiPlan {
     void* mem = nullptr;     // device: args, begin, partials, reductions
     const void* d_args = nullptr;
     const int* d_begin = nullptr;
-    const RedDesc* d_red = nullptr;
 };
 // Problems must agree on dtype, coefficient type, sector/full space and
 // configuration width (else HPHI_EINVAL); nvec must be 1.
 int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out);
-// the scalars of several recurrences (alpha/beta/evec: `stride` per problem);
-// with it, the launches that reduce the sums also take the scalar steps
-struct LzMulti {
-    LzScalars* sc;
-    double* alpha;
-    double* beta;
-    const double* evec;
-    int stride;
-};
 // blocks of a persistent grid dealt to problems in multiples of 8: begin[n + 1]
 // from the wavefront items of each (`groups`: groups of 8 blocks in all)
 std::vector<int> deal_blocks(const std::vector<int64_t>& items, int64_t groups);
 // the sums of a product from its block partials
-int launch_product_reduce(const hphi_ham* H, int n_parts, int B, const HvLaunch& L, hipStream_t st);
-int hv_multi_launch(const MultiPlan& P, const LzMulti* lz, hipStream_t st);
+// the tail of a product of n_blocks blocks: what the kernel takes along, and
+// the launches that follow if it takes nothing
+Tail product_tail_of(const HvLaunch& L, int n_blocks);
+int launch_product_tail(const HvLaunch& L, int n_blocks, hipStream_t st);
+int hv_multi_launch(const MultiPlan& P, hipStream_t st);
 // the class-blocked product when the Hamiltonian has its tables and the
 // schedule asks for it; 1 if not
 int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st);
@@ -404,11 +402,9 @@ struct UpdPlan {
     void* mem = nullptr;
     const UpdDesc* d_desc = nullptr;
     const int* d_begin = nullptr;
-    const RedDesc* d_red = nullptr;
 };
-// red_out[p]: device [1] receiving |y_p|^2
-int upd_multi_prepare(const UpdDesc* descs, double* const* red_out, int n, int dtype, UpdPlan* out);
-int upd_multi_launch(const UpdPlan& P, const LzMulti* lz, hipStream_t st);
+int upd_multi_prepare(const UpdDesc* descs, int n, int dtype, UpdPlan* out);
+int upd_multi_launch(const UpdPlan& P, hipStream_t st);
 
 // dense-block plan for clusters of M bits (cma.cpp); an error code if the
 // space or the operators do not fit

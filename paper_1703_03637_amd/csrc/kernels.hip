@@ -29,6 +29,7 @@
 
 #include "hphi_internal.h"
 #include "lane.h"
+#include "tail.h"
 
 namespace hphi {
 namespace {
@@ -249,6 +250,7 @@ struct HvArgs {
     double a, b;
     const int* stop;
     double* partials;
+    Tail tail;
     ExportArgs ex;       // element export (EXPORT instantiations only)
     // two-level low-rank table (TAB 3), compact form: with l = (a, b), b its
     // low b2 bits, rank(l) = T1c[a][class(b)] + (T2p[b] & 1023); class(b) is
@@ -712,7 +714,11 @@ __device__ __forceinline__ void hv_body(const HvArgs& A, const int blk, const in
         double acc = 0.0;
 #pragma unroll
         for (int w = 0; w < kWavesPerBlock; ++w) acc += sh[w][k][L];
-        A.partials[size_t(blk) * (kNQ * B) + threadIdx.x] = acc;
+        put_partial(&A.partials[size_t(blk) * (kNQ * B) + threadIdx.x], acc);
+    }
+    if (A.tail.mode != kTailNone) {
+        __syncthreads();   // the block sums are read
+        product_tail(A.tail, A.partials, blk, nblk, B, &sh[0][0][0]);
     }
 }
 
@@ -1020,6 +1026,7 @@ struct HvwArgs {
     double a, b;
     const int* stop;
     double* partials;
+    Tail tail;           // last pass
     int pass;            // index of this pass (element export)
     ExportArgs ex;
 };
@@ -1353,7 +1360,11 @@ __global__ __launch_bounds__(kBlock) void hvw_kernel(HvwArgs A) {
         double acc = 0.0;
 #pragma unroll
         for (int w = 0; w < kWavesPerBlock; ++w) acc += sh[w][k][L];
-        A.partials[size_t(blockIdx.x) * (kNQ * B) + threadIdx.x] = acc;
+        put_partial(&A.partials[size_t(blockIdx.x) * (kNQ * B) + threadIdx.x], acc);
+    }
+    if (A.tail.mode != kTailNone) {
+        __syncthreads();   // the block sums are read
+        product_tail(A.tail, A.partials, int(blockIdx.x), int(gridDim.x), B, &sh[0][0][0]);
     }
 }
 
@@ -1654,17 +1665,6 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const double* __re
     reduce_body(partials, n_parts, nq, int(blockIdx.x), out, flag, bit);
 }
 
-// several problems: block p * nq + q reduces quantity q of problem p
-__global__ __launch_bounds__(256) void reduce_multi_kernel(const RedDesc* __restrict__ d, int nq) {
-    const int p = int(blockIdx.x) / nq, q = int(blockIdx.x) % nq;
-    const double* partials = d[p].partials;
-    const int n_parts = d[p].n_parts;
-    double* out = d[p].out;
-    const int* stop = d[p].stop;
-    if (stop && *stop) return;
-    reduce_body(partials, n_parts, nq, q, out, d[p].flag, nq == 1 ? HPHI_NONFINITE_NORM : HPHI_NONFINITE_PRODUCT);
-}
-
 // ---- element lists from the records of an export: per row the diagonal (sum
 // of the passes' diagonal parts, in pass order) if nonzero, then the nonzero
 // off-diagonal elements in the order of the Hamiltonian's operator list
@@ -1754,40 +1754,38 @@ __global__ __launch_bounds__(256) void copy_norm_kernel(const S* __restrict__ sr
 }
 
 // y += c2 * x, |y|^2; optionally acc += ecoef * x (FP64 accumulator);
-// block blk of nblk, one partial per block
+// block blk of nblk, one partial per block; the last block takes beta
 template <typename S>
-__device__ __forceinline__ void update_body(S* __restrict__ y, const S* __restrict__ x, int64_t n,
-                                            const double* __restrict__ c2p, double* __restrict__ acc,
-                                            const double* __restrict__ ecp, double* __restrict__ partials,
-                                            int blk, int nblk) {
-    const double c2 = *c2p;
-    const double ec = acc ? *ecp : 0.0;
+__device__ __forceinline__ void update_body(const UpdDesc& D, int blk, int nblk) {
+    S* __restrict__ y = static_cast<S*>(D.y);
+    const S* __restrict__ x = static_cast<const S*>(D.x);
+    double* __restrict__ acc = D.acc;
+    const double c2 = *D.c2;
+    const double ec = acc ? *D.ec : 0.0;
     double s = 0.0;
-    for (int64_t i = int64_t(blk) * 256 + threadIdx.x; i < n; i += int64_t(nblk) * 256) {
+    for (int64_t i = int64_t(blk) * 256 + threadIdx.x; i < D.n; i += int64_t(nblk) * 256) {
         const double xv = double(x[i]);
         const S w = S(double(y[i]) + c2 * xv);
         y[i] = w;
         s += double(w) * double(w);
         if (acc) acc[i] += ec * xv;
     }
-    __shared__ double sh[256];
+    __shared__ double sh[257];
     sh[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (int(threadIdx.x) < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) partials[blk] = sh[0];
+    if (threadIdx.x == 0) put_partial(D.partials + blk, sh[0]);
+    __syncthreads();
+    update_tail(D.sc, D.tickets, D.partials, blk, nblk, D.beta, D.alpha, D.flag, sh);
 }
 
 template <typename S>
-__global__ __launch_bounds__(256) void lanczos_update_kernel(S* __restrict__ y, const S* __restrict__ x, int64_t n,
-                                                             const double* __restrict__ c2p,
-                                                             double* __restrict__ acc,
-                                                             const double* __restrict__ ecp,
-                                                             double* __restrict__ partials, const int* stop) {
-    if (stop && *stop) return;
-    update_body<S>(y, x, n, c2p, acc, ecp, partials, int(blockIdx.x), int(gridDim.x));
+__global__ __launch_bounds__(256) void lanczos_update_kernel(UpdDesc D) {
+    if (D.stop && *D.stop) return;
+    update_body<S>(D, int(blockIdx.x), int(gridDim.x));
 }
 
 // several problems: problem p owns blocks begin[p] .. begin[p+1]-1
@@ -1799,8 +1797,7 @@ __global__ __launch_bounds__(256) void lanczos_update_multi_kernel(const UpdDesc
         if (int(blockIdx.x) >= begin[q]) p = q;
     const UpdDesc D = d[p];
     if (D.stop && *D.stop) return;
-    update_body<S>(static_cast<S*>(D.y), static_cast<const S*>(D.x), D.n, D.c2, D.acc, D.ec, D.partials,
-                   int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
+    update_body<S>(D, int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
 }
 
 // w = a x + b y over n FP64 scalars (w may alias x or y), |w|^2 partials per block
@@ -1826,52 +1823,10 @@ __global__ void fill_zero_kernel(uint32_t* __restrict__ p, int64_t n_words) {
     for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n_words; i += int64_t(gridDim.x) * 256) p[i] = 0u;
 }
 
-// <O> = Re<x|Ox> / <x|x> per vector, and <x|x>
-__global__ void expect_kernel(const double* __restrict__ red, double* __restrict__ out, int nvec) {
-    const int b = threadIdx.x;
-    if (b >= nvec) return;
-    const double xx = red[0 * nvec + b], xo = red[1 * nvec + b];
-    out[b] = xo / xx;
-    out[nvec + b] = xx;
-}
-
-__global__ void tpq_obs_kernel(const double* __restrict__ red, double* __restrict__ obs, int nvec, double ns,
-                               double l, int k) {
-    const int b = threadIdx.x;
-    if (b >= nvec) return;
-    const double xx = red[0 * nvec + b], xh = red[1 * nvec + b], hh = red[2 * nvec + b],
-                 uu = red[3 * nvec + b];
-    const double uk = xh / xx / ns;
-    obs[0 * nvec + b] = uk;
-    obs[1 * nvec + b] = hh / xx / (ns * ns);
-    obs[2 * nvec + b] = (2.0 * double(k - 1) / ns) / (l - uk);
-    obs[3 * nvec + b] = 1.0 / sqrt(uu);
-}
-
-// TPQ observables of a step inside a run: the step number lives on the
-// device (graph replays advance it); the scale of the produced state goes
-// to the slot of this step's parity, where the next step reads it.
-__global__ void tpq_obs_run_kernel(const double* __restrict__ red, TpqRunState* st, double* __restrict__ obs_log,
-                                   int nvec, double ns, double l) {
-    const int b = threadIdx.x;
-    const int j = st->j;
-    if (b < nvec) {
-        const double xx = red[0 * nvec + b], xh = red[1 * nvec + b], hh = red[2 * nvec + b],
-                     uu = red[3 * nvec + b];
-        const double uk = xh / xx / ns;
-        double* o = obs_log + size_t(j) * 4 * nvec;
-        o[0 * nvec + b] = uk;
-        o[1 * nvec + b] = hh / xx / (ns * ns);
-        o[2 * nvec + b] = (2.0 * double(st->k - 1) / ns) / (l - uk);
-        const double s = 1.0 / sqrt(uu);
-        o[3 * nvec + b] = s;
-        st->scale[j & 1][b] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        st->j = j + 1;
-        st->k = st->k + 1;
-    }
+// the scalar step of a product whose sums were reduced by a launch of their own
+__global__ void tail_kernel(Tail T, int nvec) {
+    if (T.mode == kTailLanczos && T.sc->stop) return;
+    tail_step(T, T.out, nvec);
 }
 
 __global__ void tpq_run_init_kernel(TpqRunState* st, int k0) {
@@ -1896,122 +1851,34 @@ __global__ void lz_init_kernel(LzScalars* sc, const double* red, double tol, int
     sc->breakdown = nn > 0.0 ? 0 : 1;
 }
 
-// The scalar steps of one recurrence (the caller has checked sc->stop):
-// after the product, alpha_k and the update's coefficients; after the
-// update, beta_{k+1}, the stop test and the next step's scales
-__device__ void lz_after_hv_step(LzScalars* sc, const double* red, double* alpha, const double* evec) {
-    const double a = red[1];          // Re<v_k|H v_k>, v_k = s_cur * X
-    alpha[sc->k] = a;
-    sc->c2 = -a * sc->s_cur;
-    sc->ecoef = evec ? evec[sc->k] * sc->s_cur : 0.0;
-}
-
-__device__ void lz_after_update_step(LzScalars* sc, const double* red, double* beta, const double* alpha) {
-    const int k = sc->k;
-    const double b = sqrt(red[0]);
-    beta[k] = b;
-    sc->n_done = k + 1;
-    const double a = fabs(alpha[k]);
-    double scale = a > sc->beta_k ? a : sc->beta_k;
-    if (scale < 1.0) scale = 1.0;
-    if (k + 1 >= sc->n_max || b <= sc->tol * scale) {
-        sc->stop = 1;
-        if (k + 1 < sc->n_max) sc->breakdown = 1;
-        return;
-    }
-    sc->cy = -b * sc->s_cur;   // -beta_{k+1} times the scale of v_k (next step's v_{k-1})
-    sc->s_cur = 1.0 / b;
-    sc->beta_k = b;
-    sc->k = k + 1;
-}
-
-// The product's kNQ sums of one recurrence, reduced by one block with the
-// summation order of reduce_body (so they are bitwise those of
-// reduce_partials_kernel); thread 0 writes them and the flag.
-__device__ __forceinline__ void reduce_nq_body(const double* __restrict__ partials, int n_parts,
-                                               double* __restrict__ out, int32_t* flag) {
-    const int t = int(threadIdx.x);
-    double s[kNQ];
-#pragma unroll
-    for (int q = 0; q < kNQ; ++q) s[q] = 0.0;
-    for (int g = t; g < n_parts; g += 256)
-#pragma unroll
-        for (int q = 0; q < kNQ; ++q) s[q] += partials[size_t(g) * kNQ + q];
-    __shared__ double sh[kNQ][256];
-#pragma unroll
-    for (int q = 0; q < kNQ; ++q) sh[q][t] = s[q];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-#pragma unroll
-            for (int q = 0; q < kNQ; ++q) sh[q][t] += sh[q][t + w];
-        __syncthreads();
-    }
-    if (t == 0)
-        for (int q = 0; q < kNQ; ++q) {
-            out[q] = sh[q][0];
-            if (flag && !isfinite(sh[q][0])) atomicOr(flag, HPHI_NONFINITE_PRODUCT);
-        }
-}
-
-// One recurrence: the product's sums and the scalar step that reads them, in
-// one launch (the step reads the sums thread 0 has just written)
-__global__ __launch_bounds__(256) void reduce_lz_after_hv_kernel(const double* __restrict__ partials, int n_parts,
-                                                                 double* __restrict__ out, int32_t* flag,
-                                                                 LzScalars* sc, double* alpha, const double* evec) {
-    if (sc->stop) return;
-    reduce_nq_body(partials, n_parts, out, flag);
-    if (threadIdx.x == 0) lz_after_hv_step(sc, out, alpha, evec);
-}
-
-// the update's |y|^2 and the scalar step that reads it, in one launch
-__global__ __launch_bounds__(256) void reduce_lz_after_update_kernel(const double* __restrict__ partials, int n_parts,
-                                                                     double* __restrict__ out, int32_t* flag,
-                                                                     LzScalars* sc, double* beta, const double* alpha) {
-    if (sc->stop) return;
-    reduce_body(partials, n_parts, 1, 0, out, flag, HPHI_NONFINITE_NORM);
-    if (threadIdx.x == 0) lz_after_update_step(sc, out, beta, alpha);
-}
-
-// the same for several recurrences: block p takes problem p (d[p]: its
-// partials and sums; alpha/beta/evec: `stride` per problem)
-__global__ __launch_bounds__(256) void reduce_lz_after_hv_multi_kernel(const RedDesc* __restrict__ d, LzScalars* scs,
-                                                                       double* alphas, const double* evecs, int stride) {
-    const int p = int(blockIdx.x);
-    LzScalars* sc = scs + p;
-    if (sc->stop) return;
-    reduce_nq_body(d[p].partials, d[p].n_parts, d[p].out, d[p].flag);
-    if (threadIdx.x == 0)
-        lz_after_hv_step(sc, d[p].out, alphas + size_t(stride) * p, evecs ? evecs + size_t(stride) * p : nullptr);
-}
-
-__global__ __launch_bounds__(256) void reduce_lz_after_update_multi_kernel(const RedDesc* __restrict__ d,
-                                                                           LzScalars* scs, double* betas,
-                                                                           const double* alphas, int stride) {
-    const int p = int(blockIdx.x);
-    LzScalars* sc = scs + p;
-    if (sc->stop) return;
-    reduce_body(d[p].partials, d[p].n_parts, 1, 0, d[p].out, d[p].flag, HPHI_NONFINITE_NORM);
-    if (threadIdx.x == 0)
-        lz_after_update_step(sc, d[p].out, betas + size_t(stride) * p, alphas + size_t(stride) * p);
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
 
-// the product's sums (and, for one Lanczos recurrence, the scalar step that
-// reads them)
-int launch_product_reduce(const hphi_ham* H, int n_parts, int B, const HvLaunch& L, hipStream_t st) {
-    if (L.lz_sc) {
-        if (B != 1) return set_error(HPHI_EINVAL, "Lanczos step fused with the reduction needs one vector");
-        reduce_lz_after_hv_kernel<<<1, 256, 0, st>>>(H->d_partials, n_parts, L.reduce_out, H->d_flag, L.lz_sc,
-                                                     L.lz_alpha, L.lz_evec);
-    } else {
-        reduce_partials_kernel<<<kNQ * B, 256, 0, st>>>(H->d_partials, n_parts, kNQ * B, L.reduce_out, L.stop,
-                                                      H->d_flag, HPHI_NONFINITE_PRODUCT);
-    }
-    return check_hip(hipGetLastError(), "reduce launch");
+// what a product kernel of n_blocks blocks takes along
+Tail product_tail_of(const HvLaunch& L, int n_blocks) {
+    Tail T = L.tail;
+    if (L.ex || T.mode == kTailNone || n_blocks * kNQ * L.nvec > kTailMax) T.mode = kTailNone;
+    if (!T.tickets) T.tickets = L.ham->d_tickets;
+    T.flag = L.ham->d_flag;
+    return T;
+}
+
+// the launches that follow a product that took nothing along
+static int launch_separate_tail(const HvLaunch& L, int n_blocks, hipStream_t st) {
+    if (L.tail.mode == kTailNone) return HPHI_OK;
+    const int nq = kNQ * L.nvec;
+    reduce_partials_kernel<<<nq, 256, 0, st>>>(L.ham->d_partials, n_blocks, nq, L.tail.out, L.stop, L.ham->d_flag,
+                                               HPHI_NONFINITE_PRODUCT);
+    const int rc = check_hip(hipGetLastError(), "reduce launch");
+    if (rc || L.tail.mode == kTailSums) return rc;
+    tail_kernel<<<1, 64, 0, st>>>(L.tail, L.nvec);
+    return check_hip(hipGetLastError(), "product tail launch");
+}
+
+int launch_product_tail(const HvLaunch& L, int n_blocks, hipStream_t st) {
+    if (L.ex || product_tail_of(L, n_blocks).mode != kTailNone) return HPHI_OK;
+    return launch_separate_tail(L, n_blocks, st);
 }
 
 size_t dtype_size(int dtype) {
@@ -2096,6 +1963,7 @@ static int launch_hv_g(const HvLaunch& L, const Schedule& sc, size_t lds, hipStr
     A.b = L.b;
     A.stop = L.stop;
     A.partials = H->d_partials;
+    A.tail = product_tail_of(L, grid);
     if constexpr (EX) A.ex = *L.ex;
     if constexpr (TAB == 3) {
         const hphi_basis* Bs = H->basis;
@@ -2109,8 +1977,7 @@ static int launch_hv_g(const HvLaunch& L, const Schedule& sc, size_t lds, hipStr
     hv_kernel<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB, EX><<<grid, kBlock, lds, st>>>(A);
     int rc = check_hip(hipGetLastError(), "hv_kernel launch");
     if (rc) return rc;
-    if (!EX && L.reduce_out) rc = launch_product_reduce(H, grid, B, L, st);
-    return rc;
+    return launch_product_tail(L, grid, st);
 }
 
 // Table placement: 0 = pattern table and low rank table in LDS, 1 = both read
@@ -2235,9 +2102,7 @@ static int launch_hvs_t(const HvLaunch& L, int per_cu, hipStream_t st) {
     A.partials = H->d_partials;
     hvs_kernel<S, CPLX, CCOEF, B, W64><<<int(grid), kBlockS, lds, st>>>(A);
     int rc = check_hip(hipGetLastError(), "hvs_kernel launch");
-    if (rc) return rc;
-    if (L.reduce_out) rc = launch_product_reduce(H, int(grid), B, L, st);
-    return rc;
+    return rc ? rc : launch_separate_tail(L, int(grid), st);
 }
 
 // the block-staged sector product when the schedule asks for it and its
@@ -2290,6 +2155,7 @@ static int launch_hvw_t(const HvLaunch& L, const PassPlan* P, const Schedule& sc
     A.b = L.b;
     A.stop = L.stop;
     A.partials = H->d_partials;
+    A.tail = product_tail_of(L, grid);
     if constexpr (EX) {
         A.ex = *L.ex;
         if (P->n_pass > A.ex.n_pass) return set_error(HPHI_EINVAL, "element export: too many passes in the plan");
@@ -2313,8 +2179,7 @@ static int launch_hvw_t(const HvLaunch& L, const PassPlan* P, const Schedule& sc
         int rc = check_hip(hipGetLastError(), "hvw_kernel launch");
         if (rc) return rc;
     }
-    if (!EX && L.reduce_out) return launch_product_reduce(H, grid, B, L, st);
-    return HPHI_OK;
+    return launch_product_tail(L, grid, st);
 }
 
 template <typename S, bool CPLX, bool CCOEF, int B, bool EX>
@@ -2433,7 +2298,7 @@ static int launch_cma_stages(const HvLaunch& L, const CmaPlan* P, hipStream_t st
     A.a = L.a;
     A.b = L.b;
     A.sx = L.sx;
-    A.partials = L.reduce_out ? H->d_partials : nullptr;
+    A.partials = L.tail.mode != kTailNone ? H->d_partials : nullptr;
     int64_t g = int64_t(per_cu) * cu_count();
     if (g > A.n_blocks) g = A.n_blocks;
     g = ((g + 7) / 8) * 8;
@@ -2449,11 +2314,7 @@ static int launch_cma_stages(const HvLaunch& L, const CmaPlan* P, hipStream_t st
         const int rc = check_hip(hipGetLastError(), "cma_kernel launch");
         if (rc) return rc;
     }
-    if (!L.reduce_out) return HPHI_OK;
-    constexpr int B = RC / (CPLX ? 2 : 1);
-    reduce_partials_kernel<<<kNQ * B, 256, 0, st>>>(H->d_partials, int(g), kNQ * B, L.reduce_out, nullptr, H->d_flag,
-                                                      HPHI_NONFINITE_PRODUCT);
-    return check_hip(hipGetLastError(), "reduce launch");
+    return launch_separate_tail(L, int(g), st);
 }
 
 template <typename S, bool CPLX, int RC>
@@ -2559,39 +2420,26 @@ int launch_copy_norm(const void* src, void* dst, int64_t n, int dtype, double* p
     return check_hip(hipGetLastError(), "reduce launch");
 }
 
-int launch_lanczos_update(void* y, const void* x, int64_t n, int dtype, const double* c2, void* acc,
-                          const double* ecoef, double* partials, int grid, double* red, const int* stop,
-                          int32_t* flag, hipStream_t st) {
-    const int64_t ns = n * (dtype_complex(dtype) ? 2 : 1);
-    if (grid <= 0) grid = stream_grid(ns);
-    if (dtype == HPHI_F64 || dtype == HPHI_C128)
-        lanczos_update_kernel<double><<<grid, 256, 0, st>>>((double*)y, (const double*)x, ns, c2, (double*)acc,
-                                                            ecoef, partials, stop);
-    else
-        lanczos_update_kernel<float><<<grid, 256, 0, st>>>((float*)y, (const float*)x, ns, c2, (double*)acc, ecoef,
-                                                           partials, stop);
-    int rc = check_hip(hipGetLastError(), "lanczos_update launch");
-    if (rc) return rc;
-    reduce_partials_kernel<<<1, 256, 0, st>>>(partials, grid, 1, red, stop, flag, HPHI_NONFINITE_NORM);
-    return check_hip(hipGetLastError(), "reduce launch");
-}
-
-int launch_lanczos_update_lz(void* y, const void* x, int64_t n, int dtype, LzScalars* sc, void* acc,
-                             double* partials, int grid, double* red, double* beta, const double* alpha,
-                             int32_t* flag, hipStream_t st) {
-    const int64_t ns = n * (dtype_complex(dtype) ? 2 : 1);
-    if (grid <= 0) grid = stream_grid(ns);
-    const int* stop = &sc->stop;
-    if (dtype == HPHI_F64 || dtype == HPHI_C128)
-        lanczos_update_kernel<double><<<grid, 256, 0, st>>>((double*)y, (const double*)x, ns, &sc->c2, (double*)acc,
-                                                            &sc->ecoef, partials, stop);
-    else
-        lanczos_update_kernel<float><<<grid, 256, 0, st>>>((float*)y, (const float*)x, ns, &sc->c2, (double*)acc,
-                                                           &sc->ecoef, partials, stop);
-    int rc = check_hip(hipGetLastError(), "lanczos_update launch");
-    if (rc) return rc;
-    reduce_lz_after_update_kernel<<<1, 256, 0, st>>>(partials, grid, red, flag, sc, beta, alpha);
-    return check_hip(hipGetLastError(), "reduce launch");
+int launch_lanczos_update_lz(void* y, const void* x, int64_t n, int dtype, LzScalars* sc, void* acc, double* partials,
+                             int grid, double* beta, const double* alpha, int32_t* flag, uint32_t* tickets, hipStream_t st) {
+    UpdDesc D{};
+    D.tickets = tickets;
+    D.y = y;
+    D.x = x;
+    D.n = n * (dtype_complex(dtype) ? 2 : 1);
+    D.c2 = &sc->c2;
+    D.acc = static_cast<double*>(acc);
+    D.ec = &sc->ecoef;
+    D.partials = partials;
+    D.stop = &sc->stop;
+    D.flag = flag;
+    D.sc = sc;
+    D.beta = beta;
+    D.alpha = alpha;
+    if (grid <= 0) grid = stream_grid(D.n);
+    if (dtype == HPHI_F64 || dtype == HPHI_C128) lanczos_update_kernel<double><<<grid, 256, 0, st>>>(D);
+    else lanczos_update_kernel<float><<<grid, 256, 0, st>>>(D);
+    return check_hip(hipGetLastError(), "lanczos_update launch");
 }
 
 int launch_lincomb(double* w, const double* x, const double* y, int64_t n, double a, double b, double* partials,
@@ -2608,16 +2456,6 @@ int launch_fill_zero(void* p, int64_t bytes, hipStream_t st) {
     const int64_t words = bytes / 4;
     fill_zero_kernel<<<stream_grid(words), 256, 0, st>>>((uint32_t*)p, words);
     return check_hip(hipGetLastError(), "fill_zero launch");
-}
-
-int launch_expect(const double* red, double* out, int nvec, hipStream_t st) {
-    expect_kernel<<<1, 64, 0, st>>>(red, out, nvec);
-    return check_hip(hipGetLastError(), "expect launch");
-}
-
-int launch_tpq_obs(const double* red, double* obs, int nvec, double n_sites, double l, int k, hipStream_t st) {
-    tpq_obs_kernel<<<1, 64, 0, st>>>(red, obs, nvec, n_sites, l, k);
-    return check_hip(hipGetLastError(), "tpq_obs launch");
 }
 
 // The allocation-free TPQ run keeps its state here: one per device, for the
@@ -2645,12 +2483,6 @@ int tpq_static_state(TpqRunState** out) {
 int launch_tpq_run_init(TpqRunState* s, int k0, hipStream_t st) {
     tpq_run_init_kernel<<<1, 64, 0, st>>>(s, k0);
     return check_hip(hipGetLastError(), "tpq_run_init launch");
-}
-
-int launch_tpq_obs_run(const double* red, TpqRunState* s, double* obs_log, int nvec, double n_sites, double l,
-                       hipStream_t st) {
-    tpq_obs_run_kernel<<<1, 64, 0, st>>>(red, s, obs_log, nvec, n_sites, l);
-    return check_hip(hipGetLastError(), "tpq_obs_run launch");
 }
 
 int launch_lz_init(LzScalars* sc, const double* red, double tol, int n_max, hipStream_t st) {
@@ -2691,15 +2523,7 @@ static int hv_multi_product(const MultiPlan& P, hipStream_t st) {
     return set_error(HPHI_EINVAL, "bad dtype %d", P.dtype);
 }
 
-int hv_multi_launch(const MultiPlan& P, const LzMulti* lz, hipStream_t st) {
-    int rc = hv_multi_product(P, st);
-    if (rc) return rc;
-    if (lz)
-        reduce_lz_after_hv_multi_kernel<<<P.n, 256, 0, st>>>(P.d_red, lz->sc, lz->alpha, lz->evec, lz->stride);
-    else
-        reduce_multi_kernel<<<P.n * kNQ, 256, 0, st>>>(P.d_red, kNQ);
-    return check_hip(hipGetLastError(), "reduce_multi launch");
-}
+int hv_multi_launch(const MultiPlan& P, hipStream_t st) { return hv_multi_product(P, st); }
 
 std::vector<int> deal_blocks(const std::vector<int64_t>& items, int64_t groups_in) {
     const int n = int(items.size());
@@ -2777,12 +2601,10 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     const size_t a_bytes = size_t(n) * sizeof(HvArgs);
     const size_t b_off = (a_bytes + 255) / 256 * 256;
     const size_t p_off = b_off + (size_t(n + 1) * 4 + 255) / 256 * 256;
-    const size_t r_off = p_off + size_t(P.grid) * kNQ * sizeof(double);
-    const size_t total = r_off + size_t(n) * sizeof(RedDesc);
+    const size_t total = p_off + size_t(P.grid) * kNQ * sizeof(double);
     char* mem = nullptr;
     if (int rc = dev_alloc((void**)&mem, total, "hv_multi_prepare")) return rc;
     std::vector<HvArgs> args(n);
-    std::vector<RedDesc> red(n);
     double* partials = reinterpret_cast<double*>(mem + p_off);
     for (int p = 0; p < n; ++p) {
         const HvLaunch& L = Ls[p];
@@ -2800,16 +2622,11 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
         A.b = L.b;
         A.stop = L.stop;
         A.partials = partials + size_t(begin[p]) * kNQ;
-        red[p].partials = A.partials;
-        red[p].n_parts = begin[p + 1] - begin[p];
-        red[p].pad = 0;
-        red[p].out = L.reduce_out;
-        red[p].stop = L.stop;
-        red[p].flag = L.ham->d_flag;
+        A.tail = L.tail;
+        A.tail.flag = L.ham->d_flag;
     }
     hipError_t e = hipMemcpy(mem, args.data(), a_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(mem + b_off, begin.data(), size_t(n + 1) * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(mem + r_off, red.data(), size_t(n) * sizeof(RedDesc), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(mem);
         return check_hip(e, "hv_multi_prepare: upload");
@@ -2817,12 +2634,11 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     P.mem = mem;
     P.d_args = mem;
     P.d_begin = reinterpret_cast<const int*>(mem + b_off);
-    P.d_red = reinterpret_cast<const RedDesc*>(mem + r_off);
     *out = P;
     return HPHI_OK;
 }
 
-int upd_multi_prepare(const UpdDesc* descs, double* const* red_out, int n, int dtype, UpdPlan* out) {
+int upd_multi_prepare(const UpdDesc* descs, int n, int dtype, UpdPlan* out) {
     if (n < 1 || !out) return set_error(HPHI_EINVAL, "upd_multi_prepare: no problems");
     UpdPlan P;
     P.n = n;
@@ -2842,25 +2658,14 @@ int upd_multi_prepare(const UpdDesc* descs, double* const* red_out, int n, int d
     const size_t d_bytes = size_t(n) * sizeof(UpdDesc);
     const size_t b_off = (d_bytes + 255) / 256 * 256;
     const size_t p_off = b_off + (size_t(n + 1) * 4 + 255) / 256 * 256;
-    const size_t r_off = p_off + size_t(P.grid) * sizeof(double);
-    const size_t total_b = r_off + size_t(n) * sizeof(RedDesc);
+    const size_t total_b = p_off + size_t(P.grid) * sizeof(double);
     char* mem = nullptr;
     if (int rc = dev_alloc((void**)&mem, total_b, "upd_multi_prepare")) return rc;
     std::vector<UpdDesc> d(descs, descs + n);
-    std::vector<RedDesc> red(n);
     double* partials = reinterpret_cast<double*>(mem + p_off);
-    for (int p = 0; p < n; ++p) {
-        d[p].partials = partials + begin[p];
-        red[p].partials = d[p].partials;
-        red[p].n_parts = begin[p + 1] - begin[p];
-        red[p].pad = 0;
-        red[p].out = red_out[p];
-        red[p].stop = d[p].stop;
-        red[p].flag = d[p].flag;
-    }
+    for (int p = 0; p < n; ++p) d[p].partials = partials + begin[p];
     hipError_t e = hipMemcpy(mem, d.data(), d_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(mem + b_off, begin.data(), size_t(n + 1) * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(mem + r_off, red.data(), size_t(n) * sizeof(RedDesc), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(mem);
         return check_hip(e, "upd_multi_prepare: upload");
@@ -2868,23 +2673,16 @@ int upd_multi_prepare(const UpdDesc* descs, double* const* red_out, int n, int d
     P.mem = mem;
     P.d_desc = reinterpret_cast<const UpdDesc*>(mem);
     P.d_begin = reinterpret_cast<const int*>(mem + b_off);
-    P.d_red = reinterpret_cast<const RedDesc*>(mem + r_off);
     *out = P;
     return HPHI_OK;
 }
 
-int upd_multi_launch(const UpdPlan& P, const LzMulti* lz, hipStream_t st) {
+int upd_multi_launch(const UpdPlan& P, hipStream_t st) {
     if (P.fp64)
         lanczos_update_multi_kernel<double><<<P.grid, 256, 0, st>>>(P.d_desc, P.d_begin, P.n);
     else
         lanczos_update_multi_kernel<float><<<P.grid, 256, 0, st>>>(P.d_desc, P.d_begin, P.n);
-    int rc = check_hip(hipGetLastError(), "update_multi launch");
-    if (rc) return rc;
-    if (lz)
-        reduce_lz_after_update_multi_kernel<<<P.n, 256, 0, st>>>(P.d_red, lz->sc, lz->beta, lz->alpha, lz->stride);
-    else
-        reduce_multi_kernel<<<P.n, 256, 0, st>>>(P.d_red, 1);
-    return check_hip(hipGetLastError(), "reduce_multi launch");
+    return check_hip(hipGetLastError(), "update_multi launch");
 }
 
 }  // namespace hphi

@@ -1,0 +1,170 @@
+// The end of a product or update kernel: the block that finishes last sums the
+// block partials in a fixed order and takes the scalar step that reads the
+// sums, so small problems pay no further launch for either.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "hphi_internal.h"
+
+namespace hphi {
+namespace {
+
+// ---- scalar steps after the sums (also run by the separate launches)
+
+// after the product: alpha_k and the update's coefficients
+__device__ __forceinline__ void lz_after_hv_step(LzScalars* sc, const double* red, double* alpha, const double* evec) {
+    const double a = red[1];          // Re<v_k|H v_k>, v_k = s_cur * X
+    alpha[sc->k] = a;
+    sc->c2 = -a * sc->s_cur;
+    sc->ecoef = evec ? evec[sc->k] * sc->s_cur : 0.0;
+}
+
+// after the update: beta_{k+1}, the stop test and the next step's scales
+__device__ __forceinline__ void lz_after_update_step(LzScalars* sc, const double* red, double* beta, const double* alpha) {
+    const int k = sc->k;
+    const double b = sqrt(red[0]);
+    beta[k] = b;
+    sc->n_done = k + 1;
+    const double a = fabs(alpha[k]);
+    double scale = a > sc->beta_k ? a : sc->beta_k;
+    if (scale < 1.0) scale = 1.0;
+    if (k + 1 >= sc->n_max || b <= sc->tol * scale) {
+        sc->stop = 1;
+        if (k + 1 < sc->n_max) sc->breakdown = 1;
+        return;
+    }
+    sc->cy = -b * sc->s_cur;   // -beta_{k+1} times the scale of v_k (next step's v_{k-1})
+    sc->s_cur = 1.0 / b;
+    sc->beta_k = b;
+    sc->k = k + 1;
+}
+
+// TPQ observables of vector b of a step with index k; returns 1 / |phi|
+__device__ __forceinline__ double tpq_obs_step(const double* red, double* obs, int nvec, int b, double ns, double l, int k) {
+    const double xx = red[0 * nvec + b], xh = red[1 * nvec + b], hh = red[2 * nvec + b], uu = red[3 * nvec + b];
+    const double uk = xh / xx / ns;
+    const double s = 1.0 / sqrt(uu);
+    obs[0 * nvec + b] = uk;
+    obs[1 * nvec + b] = hh / xx / (ns * ns);
+    obs[2 * nvec + b] = (2.0 * double(k - 1) / ns) / (l - uk);
+    obs[3 * nvec + b] = s;
+    return s;
+}
+
+// <O> = Re<x|Ox> / <x|x> per vector, and <x|x>
+__device__ __forceinline__ void expect_step(const double* red, double* out, int nvec, int b) {
+    const double xx = red[0 * nvec + b], xo = red[1 * nvec + b];
+    out[b] = xo / xx;
+    out[nvec + b] = xx;
+}
+
+// The scalar step of `T` on the sums red[q * nvec + b] (all threads of one block)
+__device__ __forceinline__ void tail_step(const Tail& T, const double* red, int nvec) {
+    const int t = int(threadIdx.x);
+    if (T.mode == kTailLanczos) {
+        if (t == 0) lz_after_hv_step(T.sc, red, T.alpha, T.evec);
+    } else if (T.mode == kTailTpq) {
+        if (t < nvec) tpq_obs_step(red, T.obs, nvec, t, T.ns, T.l, T.k);
+    } else if (T.mode == kTailTpqRun) {
+        // the step number lives on the device (graph replays advance it); the
+        // scale of the produced state goes to the slot of this step's parity
+        const int j = T.run->j, k = T.run->k;
+        if (t < nvec) T.run->scale[j & 1][t] = tpq_obs_step(red, T.obs + size_t(j) * 4 * nvec, nvec, t, T.ns, T.l, k);
+        __syncthreads();
+        if (t == 0) {
+            T.run->j = j + 1;
+            T.run->k = k + 1;
+        }
+    } else if (T.mode == kTailExpect) {
+        if (t < nvec) expect_step(red, T.obs, nvec, t);
+    }
+}
+
+// A block partial: written through to where every XCD sees it, so that no block
+// has to write its whole L2 back (a release fence at device scope does, and cost
+// 20 to 30 us per launch of a few hundred blocks)
+__device__ __forceinline__ void put_partial(double* p, double x) {
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ double get_partial(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Called by every thread of every block (256 threads) after wave 0 of the block
+// has stored its partials with put_partial.  True for the threads of the last
+// block to arrive, which then reads the partials of all with get_partial.
+// Two levels of tickets, 32 blocks to one, each in a line of its own: a single
+// one serializes the atomics of all blocks (1,024 blocks: 15 to 20 us).
+// `flag`: one word of LDS.
+__device__ __forceinline__ bool tail_last(uint32_t* tickets, int blk, int n_blocks, int* flag) {
+    if (threadIdx.x < 64) {
+        // the wave's stores have arrived before its ticket counts
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (threadIdx.x == 0) {
+            const int g = blk >> 5, n_g = (n_blocks + 31) >> 5;
+            const uint32_t size = uint32_t(g + 1 < n_g ? 32 : n_blocks - 32 * g);
+            uint32_t* tg = tickets + size_t(1 + g) * kTicketStride;
+            int last = 0;
+            if (__hip_atomic_fetch_add(tg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == size - 1) {
+                __hip_atomic_store(tg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = __hip_atomic_fetch_add(tickets, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == uint32_t(n_g - 1);
+                if (last) __hip_atomic_store(tickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            *flag = last;
+        }
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
+// Sums of partials[g * nq + q], g < n_parts, into lds[q]: the threads of a
+// quantity take every (256 / nq)-th partial, then a fixed tree.  nq divides 256.
+__device__ __forceinline__ void tail_sums(const double* partials, int n_parts, int nq, double* lds) {
+    const int t = int(threadIdx.x), q = t % nq, s0 = t / nq, ns = 256 / nq;
+    double s = 0.0;
+    int g = s0;
+    for (; g + 7 * ns < n_parts; g += 8 * ns) {
+        double x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = get_partial(partials + size_t(g + j * ns) * nq + q);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += x[j];
+    }
+    for (; g < n_parts; g += ns) s += get_partial(partials + size_t(g) * nq + q);
+    lds[t] = s;
+    __syncthreads();
+    for (int w = ns / 2; w > 0; w >>= 1) {
+        if (s0 < w) lds[t] += lds[t + w * nq];
+        __syncthreads();
+    }
+}
+
+// The tail of a product over nvec vectors.  `lds`: 257 doubles of LDS that no
+// thread of the block reads any more.
+__device__ __forceinline__ void product_tail(const Tail& T, const double* partials, int blk, int n_blocks, int nvec, double* lds) {
+    if (T.mode == kTailNone) return;
+    if (!tail_last(T.tickets, blk, n_blocks, reinterpret_cast<int*>(lds + 256))) return;
+    const int nq = kNQ * nvec, t = int(threadIdx.x);
+    tail_sums(partials, n_blocks, nq, lds);
+    if (t < nq) {
+        if (T.out) T.out[t] = lds[t];
+        if (T.flag && !isfinite(lds[t])) atomicOr(T.flag, HPHI_NONFINITE_PRODUCT);
+    }
+    tail_step(T, lds, nvec);
+}
+
+// The tail of a Lanczos update: |y|^2, then beta and the next scales
+__device__ __forceinline__ void update_tail(LzScalars* sc, uint32_t* tickets, const double* partials, int blk, int n_blocks, double* beta,
+                                            const double* alpha, int32_t* flag, double* lds) {
+    if (!tail_last(tickets, blk, n_blocks, reinterpret_cast<int*>(lds + 256))) return;
+    tail_sums(partials, n_blocks, 1, lds);
+    if (threadIdx.x == 0) {
+        if (flag && !isfinite(lds[0])) atomicOr(flag, HPHI_NONFINITE_NORM);
+        lz_after_update_step(sc, lds, beta, alpha);
+    }
+}
+
+}  // namespace
+}  // namespace hphi
