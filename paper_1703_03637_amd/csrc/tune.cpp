@@ -38,7 +38,9 @@ int env_int(const char* name, int dflt) {
 //     window passes pay sooner: up to 32 MB, 18 sites 81 -> 75), else two
 //     passes of 1 MB windows (complex64 x 16, 24 sites 6181 -> 4896; x 4, 1393
 //     -> 1314).  Rows of 256 bytes keep three passes of 2 MB (24 sites 14970
-//     against 14697, 20 sites 517 against 567).
+//     against 14697, 20 sites 517 against 567), and so do 8 or 16 real FP32
+//     vectors, split over lanes (x 16, 24 sites 2768 against 2863; x 8, 26 sites
+//     6240 against 6463).
 Schedule default_schedule(const hphi_basis* B, int nvec, int dtype) {
     Schedule s;
     s.windowed = 1;
@@ -48,7 +50,7 @@ Schedule default_schedule(const hphi_basis* B, int nvec, int dtype) {
     const size_t bytes = row * size_t(B->dim);
     const bool full = B->dev.sector == 0;
     if (full && (row <= 16 || bytes <= (size_t(row <= 64 ? 256 : 32) << 20))) s.max_passes = 1;
-    else if (full && row <= 128) {
+    else if (full && row <= 128 && (nvec < 8 || row > 64)) {
         s.window_kb = 1024;
         s.max_passes = 2;
     }
