@@ -235,7 +235,9 @@ int hphi_hv(const hphi_ham* ham, const void* v, void* u, int64_t nvec, int32_t d
  * than 32 bits the two-level low-rank table --, 2 = only the pattern table
  * in LDS, 0 = read from global memory), nt_streams (windowed kernel, nvec >= 8: 1 = partial
  * sums, output and staged copies move with non-temporal hints so they do
- * not evict the gather window from L2), sector_blocks (sector bases: 1 = the
+ * not evict the gather window from L2), sector_blocks (sector bases: 2 = the
+ * class-blocked kernel, which shares the decode of a low half among the high
+ * halves that need it, where the Hamiltonian is real and unconditional, 1 = the
  * block-staged kernel that keeps each high-half block of rows in LDS, 0 =
  * the per-tile kernel), microseconds per product call (9 ints in all).  If the
  * environment variable HPHI_TUNE_CACHE names a file, the choice is
@@ -362,8 +364,8 @@ int hphi_lanczos(const hphi_ham* const* hams, int32_t n_hams, const hphi_lanczos
  *          four vectors of the method)
  *   res    host: E = <x|H|x>, variance, residual |Hx - Ex| of the result, the
  *          CG iterations taken, info = HPHI_OK or HPHI_INFO_MAXITER
- * opts NULL = {1e-6, 2, 1000, 1e-12}.  Synchronizes `stream` (each CG step
- * reads its two FP64 scalars on the host). */
+ * opts NULL = {1e-6, 2, 1000, 1e-12}.  Synchronizes `stream` (the scalars
+ * of the solve stay on the device; the host reads them every few steps). */
 typedef struct {
     double shift;         /* added to e_approx (> 0)                            */
     int32_t n_inverse;    /* inverse-iteration steps (>= 1)                     */

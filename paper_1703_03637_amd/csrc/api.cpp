@@ -882,9 +882,13 @@ extern "C" int hphi_cg_refine(const hphi_ham* ham, void* x, int32_t dtype, doubl
     double* P = R + n;
     double* Q = P + n;
     double* mem = nullptr;
-    if (int rc0 = dev_alloc((void**)&mem, (2048 + 64) * sizeof(double), "hphi_cg_refine: workspace")) return rc0;
+    if (int rc0 = dev_alloc((void**)&mem, (2048 + 64 + 32) * sizeof(double) + size_t(kTickets) * 4,
+                            "hphi_cg_refine: workspace"))
+        return rc0;
     double* partials = mem;
     double* red = mem + 2048;                // [0..3] product sums, [8] a norm
+    CgScalars* cg = reinterpret_cast<CgScalars*>(mem + 2048 + 64);
+    uint32_t* tickets = reinterpret_cast<uint32_t*>(mem + 2048 + 64 + 32);
     const double Ep = e_approx + o.shift;
     int rc = HPHI_OK;
     res->cg_iters = 0;
@@ -894,7 +898,7 @@ extern "C" int hphi_cg_refine(const hphi_ham* ham, void* x, int32_t dtype, doubl
         return r ? r : check_hip(hipStreamSynchronize(st), "cg sync");
     };
     // A v = (H - E') v in one product call: a = 1, b = -E'
-    auto apply = [&](const double* v, double* u, double* pap) {
+    auto apply = [&](const double* v, double* u, CgScalars* cg) {
         HvLaunch L{};
         L.ham = ham;
         L.v = v;
@@ -904,41 +908,37 @@ extern "C" int hphi_cg_refine(const hphi_ham* ham, void* x, int32_t dtype, doubl
         L.nvec = 1;
         L.dtype = dtype;
         set_sums(L, red);
-        int r = launch_hv(L, st);
-        double q[2];
-        if (!r) r = host(q, red, 2);
-        if (!r) *pap = q[1] - Ep * q[0];     // <v|Hv> - E' <v|v>
-        return r;
+        if (cg) {     // a CG step: alpha from the sums, nothing once the solve has ended
+            L.stop = &cg->stop;
+            L.tail.mode = kTailCg;
+            L.tail.cg = cg;
+            L.tail.l = Ep;
+        }
+        return launch_hv(L, st);
     };
+    rc = launch_fill_zero(tickets, int64_t(kTickets) * 4, st);
     for (int it = 0; it < o.n_inverse && !rc; ++it) {
         // CG for A y = b with b = y_k (|b| = 1) from x_0 = y_k: r = b - A b
-        double pap = 0.0, rr = 0.0;
-        rc = apply(X, Q, &pap);
+        rc = apply(X, Q, nullptr);
         if (!rc) rc = launch_lincomb(R, X, Q, n, 1.0, -1.0, partials, red + 8, st);
-        if (!rc) rc = host(&rr, red + 8, 1);
+        if (!rc) rc = launch_cg_init(cg, red + 8, o.cg_tol, o.cg_max_iter, st);
         if (!rc) rc = launch_lincomb(P, R, R, n, 1.0, 0.0, partials, nullptr, st);
-        int j = 0;
-        bool done = std::sqrt(rr) <= o.cg_tol;
-        for (; !rc && !done && j < o.cg_max_iter; ++j) {
-            rc = apply(P, Q, &pap);
-            if (rc) break;
-            if (!std::isfinite(pap) || pap == 0.0) break;    // breakdown: keep the current iterate
-            const double alpha = rr / pap;
-            rc = launch_lincomb(X, X, P, n, 1.0, alpha, partials, nullptr, st);
-            double rn = 0.0;
-            if (!rc) rc = launch_lincomb(R, R, Q, n, 1.0, -alpha, partials, red + 8, st);
-            if (!rc) rc = host(&rn, red + 8, 1);
-            if (rc) break;
-            if (std::sqrt(rn) <= o.cg_tol) {
-                done = true;
-                ++j;
-                break;
+        // The scalars stay on the device; the host waits for them after 8 steps,
+        // then every 16.  Steps enqueued beyond the end of the solve return at
+        // once (three launches each).
+        CgScalars h{};
+        for (int j = 0, chunk = 8; !rc && j < o.cg_max_iter; chunk = 16) {
+            const int end = std::min(o.cg_max_iter, j + chunk);
+            for (; !rc && j < end; ++j) {
+                rc = apply(P, Q, cg);
+                if (!rc) rc = launch_cg_update(X, R, P, Q, n, cg, partials, tickets, st);
             }
-            rc = launch_lincomb(P, R, P, n, 1.0, rn / rr, partials, nullptr, st);
-            rr = rn;
+            if (!rc) rc = check_hip(hipMemcpyAsync(&h, cg, sizeof(h), hipMemcpyDeviceToHost, st), "copy scalars");
+            if (!rc) rc = check_hip(hipStreamSynchronize(st), "cg sync");
+            if (h.stop) break;
         }
-        res->cg_iters += j;
-        if (!rc && !done && j >= o.cg_max_iter) res->info = HPHI_INFO_MAXITER;
+        res->cg_iters += h.iters;
+        if (!rc && !h.done && h.iters >= o.cg_max_iter) res->info = HPHI_INFO_MAXITER;
         // normalize y_{k+1}
         double xx = 0.0;
         if (!rc) rc = launch_lincomb(X, X, X, n, 1.0, 0.0, partials, red + 8, st);

@@ -259,8 +259,9 @@ struct ExportArgs {
 // launch wrappers (kernels.hip)
 struct LzScalars;
 struct TpqRunState;
+struct CgScalars;
 // What follows a product's sums: the scalar step of its caller.
-enum { kTailNone = 0, kTailSums, kTailLanczos, kTailTpq, kTailTpqRun, kTailExpect };
+enum { kTailNone = 0, kTailSums, kTailLanczos, kTailTpq, kTailTpqRun, kTailExpect, kTailCg };
 constexpr int kTicketStride = 32;                       // a 128-byte line each
 constexpr int kTickets = (1 + (kMaxGrid + 31) / 32) * kTicketStride;
 struct Tail {
@@ -274,8 +275,20 @@ struct Tail {
     const double* evec = nullptr;
     double* obs = nullptr;          // TPQ observables (of the run: the log), or <O> and <x|x>
     TpqRunState* run = nullptr;
+    CgScalars* cg = nullptr;        // CG: <p|A p> and alpha, A = H - l
     double ns = 0.0, l = 0.0;
 };
+// device scalars of one CG solve
+struct CgScalars {
+    double rr, alpha, beta, tol;
+    int32_t n_max, iters;     // iterations allowed and taken
+    int32_t stop, done;       // ended; converged
+    int32_t pad;
+};
+int launch_cg_init(CgScalars* c, const double* rr, double tol, int n_max, hipStream_t st);
+// x += alpha p, r -= alpha q, |r|^2 with the stop test and beta, then p = r + beta p
+int launch_cg_update(double* x, double* r, double* p, const double* q, int64_t n, CgScalars* c, double* partials,
+                     uint32_t* tickets, hipStream_t st);
 // The last block of the product takes the sums where they are few; more of
 // them are summed faster by a launch of one block per sum.
 constexpr int kTailMax = 16384;

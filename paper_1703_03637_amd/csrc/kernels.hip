@@ -1825,7 +1825,7 @@ __global__ void fill_zero_kernel(uint32_t* __restrict__ p, int64_t n_words) {
 
 // the scalar step of a product whose sums were reduced by a launch of their own
 __global__ void tail_kernel(Tail T, int nvec) {
-    if (T.mode == kTailLanczos && T.sc->stop) return;
+    if ((T.mode == kTailLanczos && T.sc->stop) || (T.mode == kTailCg && T.cg->stop)) return;
     tail_step(T, T.out, nvec);
 }
 

@@ -59,6 +59,14 @@ __device__ __forceinline__ void expect_step(const double* red, double* out, int 
     out[nvec + b] = xx;
 }
 
+// after the product of a CG step: <p|A p>, A = H - l; zero or non-finite ends
+// the solve with the current iterate
+__device__ __forceinline__ void cg_after_hv_step(CgScalars* c, const double* red, double l) {
+    const double pap = red[1] - l * red[0];
+    if (!isfinite(pap) || pap == 0.0) c->stop = 1;
+    else c->alpha = c->rr / pap;
+}
+
 // The scalar step of `T` on the sums red[q * nvec + b] (all threads of one block)
 __device__ __forceinline__ void tail_step(const Tail& T, const double* red, int nvec) {
     const int t = int(threadIdx.x);
@@ -76,6 +84,8 @@ __device__ __forceinline__ void tail_step(const Tail& T, const double* red, int 
             T.run->j = j + 1;
             T.run->k = k + 1;
         }
+    } else if (T.mode == kTailCg) {
+        if (t == 0) cg_after_hv_step(T.cg, red, T.l);
     } else if (T.mode == kTailExpect) {
         if (t < nvec) expect_step(red, T.obs, nvec, t);
     }
