@@ -48,12 +48,6 @@ struct GGroups {
     uint32_t items[8];
 };
 
-// a partner block: its first row and the signed element
-struct GEnt {
-    int64_t row0;
-    double c;
-};
-
 // operator inside the low half: flips m (two bits), sign parity of l & sm;
 // pos/neg: its element and its negative in the coefficient list
 struct GLow {
@@ -78,7 +72,7 @@ struct GCross {
 // operator as the table builder reads it
 struct GBuildOp {
     uint64_t m_hi, sm_hi;     // flip and sign masks in the high half
-    double c;
+    int32_t pos, neg;         // its element and its negative in the coefficient list
     int32_t op, pad;
 };
 
@@ -90,6 +84,9 @@ struct GBuildDiag {
     double d[4];
 };
 
+// rows of a padded list: the batches of a kernel and one of reading ahead
+constexpr int group_rows(int n) { return (n + kGroupPad - 1) / kGroupPad * kGroupPad + kGroupPad; }
+
 struct GroupPlan {
     int n_ll = 0, n_lh = 0, n_col = 0, n_ci = 0, n_hh = 0, hh_stride = 0, n_coef = 0;
     uint32_t n_slot = 0, n_low = 0;
@@ -99,15 +96,15 @@ struct GroupPlan {
     const uint32_t* hval = nullptr;
     const uint32_t* n_ent = nullptr;
     const double* dhi = nullptr;
-    const GEnt* hh = nullptr;        // [n_slot][hh_stride]
+    const uint64_t* hh = nullptr;    // [n_slot][hh_stride] first row of the partner block | coefficient << 48
     const int64_t* lhe = nullptr;    // [n_lh][n_slot] first row of the partner block | high-half sign << 63
     const double* w = nullptr;       // [n_ci][n_slot]
     const uint32_t* ci = nullptr;    // [n_ci] low bit of each cross-diagonal column; + 32: it enters as a sign
     const double* dlo = nullptr;     // [n_low], the order of `lows`
-    const uint32_t* nbr = nullptr;   // [n_ll, padded][n_low]: partner rank | coefficient << 24 (0: row not touched)
+    const uint32_t* nbr = nullptr;   // [n_ll, padded twice][n_low]: partner rank | coefficient << 24 (0: row not touched)
     const uint32_t* xnb = nullptr;   // [n_col][n_low]: rank of l ^ mi | (sign << 30) | (bit of l << 31)
     const double* coef = nullptr;    // [n_coef], coef[0] = 0
-    const GCross* lh = nullptr;      // [n_lh], padded
+    const GCross* lh = nullptr;      // [n_lh], padded; one padding more
     // element export
     const GLow* ll_ops = nullptr;    // [n_ll]
     const GBuildOp* hh_ops = nullptr;
@@ -138,7 +135,7 @@ struct GroupBuild {
     uint32_t* hval;
     uint32_t* n_ent;
     double* dhi_out;
-    GEnt* hh;
+    uint64_t* hh;
     int64_t* lhe;
     double* w;
     double* dlo;

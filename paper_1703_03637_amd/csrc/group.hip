@@ -17,6 +17,9 @@ int launch_hvg_multi_f32(const HvgArgs* d_args, const int* d_begin, int n, int n
 int launch_hvg_multi_f64(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
                          hipStream_t st);
 
+// rows from which only groups of four and more high halves are used
+static constexpr int64_t kGroupLarge = int64_t(1) << 22;
+
 namespace {
 
 // a sum with its rounding errors carried along (Knuth's two-sum)
@@ -51,16 +54,16 @@ __global__ __launch_bounds__(256) void group_high_kernel(GroupBuild G, BasisDev 
     }
     G.dhi_out[p] = dhi.value();
     uint32_t n = 0;
-    GEnt* hh = G.hh + size_t(p) * size_t(G.hh_stride);
+    uint64_t* hh = G.hh + size_t(p) * size_t(G.hh_stride);
     for (int o = 0; o < G.n_hh; ++o) {
         const GBuildOp& op = G.op_hh[o];
         const uint64_t x = h & op.m_hi;
         if (x == 0 || x == op.m_hi) continue;
-        const double s = (__popcll(h & op.sm_hi) & 1) ? -op.c : op.c;
-        hh[n++] = GEnt{bs.j_hi[h ^ op.m_hi], s};
+        const uint64_t c = uint64_t((__popcll(h & op.sm_hi) & 1) ? op.neg : op.pos);
+        hh[n++] = uint64_t(bs.j_hi[h ^ op.m_hi]) | (c << 48);
     }
     G.n_ent[p] = n;
-    for (; n < uint32_t(G.hh_stride); ++n) hh[n] = GEnt{row0, 0.0};
+    for (; n < uint32_t(G.hh_stride); ++n) hh[n] = uint64_t(row0);
     for (int o = 0; o < G.n_lh; ++o) {
         const GBuildOp& op = G.op_lh[o];
         const int64_t t = bs.j_hi[h ^ op.m_hi];
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(256) void group_low_kernel(GroupBuild G, BasisDev b
         const uint32_t ci = uint32_t((__popc(l & op.sm) & 1) ? op.neg : op.pos);
         G.nbr[size_t(o) * n_low + i] = x == 0 || x == op.m ? bs.j_lo[l] : bs.j_lo[l ^ op.m] | (ci << 24);
     }
-    const int rows = (G.n_ll + kGroupPad - 1) / kGroupPad * kGroupPad;
+    const int rows = group_rows(G.n_ll);
     for (int o = G.n_ll; o < rows; ++o) G.nbr[size_t(o) * n_low + i] = bs.j_lo[l];
     for (int k = 0; k < G.n_col; ++k) {
         const GColumn col = G.col[k];
@@ -134,6 +137,7 @@ bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_c
         uint32_t mi, sm;
         int j;
         GBuildOp b;
+        double c;
     };
     std::vector<Cross> lh;
     out.coef.assign(1, 0.0);
@@ -154,9 +158,9 @@ bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_c
                 out.ll.push_back(GLow{uint32_t(xl), uint32_t(sl), coef_at(op.cr[1]), coef_at(-op.cr[1]), int32_t(o), 0});
             } else if (xl == 0) {
                 if (sl) return false;
-                out.hh.push_back(GBuildOp{xh, sh, op.cr[1], int32_t(o), 0});
+                out.hh.push_back(GBuildOp{xh, sh, coef_at(op.cr[1]), coef_at(-op.cr[1]), int32_t(o), 0});
             } else {
-                lh.push_back({uint32_t(xl), uint32_t(sl), __builtin_ctzll(xh), GBuildOp{xh, sh, op.cr[1], int32_t(o), 0}});
+                lh.push_back({uint32_t(xl), uint32_t(sl), __builtin_ctzll(xh), GBuildOp{xh, sh, 0, 0, int32_t(o), 0}, op.cr[1]});
             }
         }
         if (op.d[0] == 0.0 && op.d[1] == 0.0 && op.d[2] == 0.0 && op.d[3] == 0.0) continue;
@@ -207,14 +211,14 @@ bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_c
         for (size_t b = a; b < lh.size(); ++b) {
             if (done[b] || lh[b].mi != lh[a].mi || lh[b].sm != lh[a].sm) continue;
             done[b] = 1;
-            out.lh.push_back(GCross{lh[b].j, int32_t(out.col.size()), lh[b].b.op, 0, lh[b].b.c});
+            out.lh.push_back(GCross{lh[b].j, int32_t(out.col.size()), lh[b].b.op, 0, lh[b].c});
             out.lh_build.push_back(lh[b].b);
         }
         out.col.push_back(GColumn{lh[a].mi, lh[a].sm});
     }
     while (out.lh.size() % size_t(kGroupPad)) {
         out.lh.push_back(GCross{0, 0, -1, 0, 0.0});
-        out.lh_build.push_back(GBuildOp{0, 0, 0.0, -1, 0});
+        out.lh_build.push_back(GBuildOp{0, 0, 0, 0, -1, 0});
     }
     // the tables stay below half of an 8-byte vector, or small
     const size_t n_low = size_t(1) << b_lo, n_slot = size_t(B->grp.n_slot);
@@ -285,7 +289,7 @@ void group_order(const hphi_basis* B, const std::vector<uint64_t>& h_val, const 
     };
     put(hord.data(), hord.size() * 4);
     gb.cls_at = put(cls.data(), cls.size() * sizeof(GClass));
-    for (int i = 0; i < 4; ++i) {
+    for (int i = B->dim >= kGroupLarge ? 2 : 0; i < 4; ++i) {
         const uint32_t K = 1u << i;
         std::vector<GGroup> of[8];
         uint32_t items[8] = {};
@@ -326,9 +330,9 @@ int group_build(const hphi_basis* B, const GroupBuild& G) {
 static int group_k(int ns, int dtype, int64_t rows) {
     if (const char* e = std::getenv("HPHI_GROUP_K")) {
         const int k = std::atoi(e);
-        if (k == 1 || k == 2 || k == 4 || (k == 8 && ns <= 2)) return k;
+        if (((k == 1 || k == 2) && rows < kGroupLarge) || k == 4 || (k == 8 && ns <= 2)) return k;
     }
-    if (rows >= (int64_t(1) << 22)) return ns <= 2 ? 8 : 4;
+    if (rows >= kGroupLarge) return ns <= 2 ? 8 : 4;
     return rows >= (int64_t(1) << 19) ? 4 : rows >= (int64_t(1) << 15) ? 2 : 1;
 }
 

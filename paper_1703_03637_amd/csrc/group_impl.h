@@ -59,8 +59,8 @@ __device__ __forceinline__ void export_rows(const HvgArgs& A, uint32_t p0, uint3
         for (int o = 0; o < P.n_hh; ++o) {
             const uint32_t m = uint32_t(P.hh_ops[o].m_hi), x = hval & m;
             if (x == 0 || x == m) continue;
-            const GEnt t = P.hh[size_t(p) * size_t(P.hh_stride) + e++];
-            put(P.hh_ops[o].op, t.row0 + int64_t(r), t.c);
+            const uint64_t t = P.hh[size_t(p) * size_t(P.hh_stride) + e++];
+            put(P.hh_ops[o].op, int64_t((t << 16) >> 16) + int64_t(r), P.coef[t >> 48]);
         }
         for (int o = 0; o < P.n_lh; ++o) {
             if (P.lh[o].op < 0) continue;
@@ -73,6 +73,9 @@ __device__ __forceinline__ void export_rows(const HvgArgs& A, uint32_t p0, uint3
         A.ex.diag[size_t(row) * size_t(A.ex.n_pass)] = dd[k];
     }
 }
+
+// items of `size` bytes that fill `bytes`, between 1 and `most`
+constexpr int group_batch(int bytes, int size, int most) { return size >= bytes ? 1 : bytes / size > most ? most : bytes / size; }
 
 // One wavefront: a tile of 64 low halves of one class (LPR passes of 64 / LPR
 // rows, a row shared by LPR lanes with NE scalars each) times K high halves.
@@ -87,12 +90,22 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
     constexpr int RPW = 64 / LPR;
     constexpr int LOGL = Log2<LPR>::value;
     constexpr int LOGE = Log2<NE>::value;
-    // gathers in flight: EB list entries times K blocks, HB partner blocks of
-    // one high half (about 32 registers each)
-    constexpr int EB = K * Ly::LB >= 64 ? 1 : 64 / (K * Ly::LB) > kGroupPad ? kGroupPad : 64 / (K * Ly::LB);
-    constexpr int OB = K * Ly::LB >= 32 ? 1 : 32 / (K * Ly::LB) > kGroupPad ? kGroupPad : 32 / (K * Ly::LB);
-    constexpr int HB = 64 / Ly::LB >= 16 ? 16 : 64 / Ly::LB <= 4 ? 4 : 64 / Ly::LB;
-    static_assert(kGroupPad % EB == 0 && kGroupPad % OB == 0 && HB % kGroupEnt == 0, "padding covers the batches");
+    // Batches: EB list entries, OB cross operators and HB partner blocks of each
+    // high half are gathered for the K blocks before any is accumulated, by
+    // bytes per lane.  Narrow FP32 rows are bound by the L1's in-order returns
+    // (its pending stalls take 60-70% of the cycles) and lose with more in
+    // flight per wave: 1.25e9 FP32 rows, K = 8, LL/LH/HH = 32/16/64 36.2 ms,
+    // 64/32/64 37.8, 128/64/64 60; rows of four scalars and more are bound by
+    // the traffic between L2 and the fabric (6.2 TB/s on four complex64
+    // vectors) and want it full: 64/32/64 81.0 ms, 128/64/128 78.2.
+    constexpr int LL = Ly::LB >= 16 ? 128 : sizeof(S) == 4 ? 32 : 64;
+    constexpr int LH = Ly::LB >= 16 ? 64 : sizeof(S) == 4 ? 16 : 32;
+    constexpr int HH = Ly::LB >= 16 ? 128 : 64;
+    constexpr int EB = group_batch(LL, K * Ly::LB, kGroupPad);
+    constexpr int OB = group_batch(LH, K * Ly::LB, kGroupPad);
+    constexpr int HB = group_batch(HH, K * Ly::LB, kGroupEnt);
+    constexpr int LOGB = Log2<Ly::RB>::value;
+    static_assert(kGroupPad % EB == 0 && kGroupPad % OB == 0 && kGroupEnt % HB == 0, "padding covers the batches");
     if (A.stop && *A.stop) return;
 
     const int lane = threadIdx.x & 63;
@@ -161,7 +174,7 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
                 const int n_ll = A.plan.n_ll;
                 uint32_t ent[EB];
 #pragma unroll
-                for (int j = 0; j < EB; ++j) ent[j] = n_ll ? nb[size_t(j) * n_low] : 0u;
+                for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(j) * n_low];
                 const char* vb[K];
                 {
                     const ConstPtr<int64_t> r0 = phase((ConstPtr<int64_t>)(A.plan.row0) + p0);
@@ -186,10 +199,8 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
                             for (int k = 0; k < K; ++k)
                                 load_at<S, NE, LPR>(vb[k] + off[j], g[j][k]);
                         }
-                    if (o + EB < n_ll) {
 #pragma unroll
-                        for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(o + EB + j) * n_low];
-                    }
+                    for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(o + EB + j) * n_low];   // the list is padded
 #pragma unroll
                     for (int j = 0; j < EB; ++j)
                         if (act[j]) {
@@ -201,31 +212,36 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
                 }
 
                 // ---- operators inside the high half: per high half a list of
-                // partner blocks, read at the row's own rank
+                // partner blocks, read at the row's own rank.  The K lists run
+                // together, HB entries of each at a time, to the end of the
+                // longest; past its end a list names the block itself and the
+                // zero element.  Without branches the scalar loads of a batch
+                // go out together, and the elements arrive behind the gathers.
+                {
+                    const ConstPtr<uint32_t> np = (ConstPtr<uint32_t>)(A.plan.n_ent) + p0;
+                    uint32_t n = 0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const uint32_t n = ((ConstPtr<uint32_t>)(A.plan.n_ent))[p0 + k];
-                    const ConstPtr<GEnt> he = (ConstPtr<GEnt>)(A.plan.hh) + size_t(p0 + k) * uint32_t(A.plan.hh_stride);
+                    for (int k = 0; k < K; ++k) n = np[k] > n ? np[k] : n;
+                    const uint32_t stride = uint32_t(A.plan.hh_stride);
+                    const ConstPtr<uint64_t> he = (ConstPtr<uint64_t>)(A.plan.hh) + size_t(p0) * stride;
+                    const ConstPtr<double> hc = (ConstPtr<double>)(A.plan.coef);
                     for (uint32_t e0 = 0; e0 < n; e0 += HB) {
-                        alignas(16) S g[HB][NE];
-                        double cf[HB];
+                        alignas(16) S g[K][HB][NE];
+                        double cf[K][HB];
 #pragma unroll
-                        for (int b = 0; b < HB; b += kGroupEnt)
-                            if (b == 0 || e0 + b < n) {
+                        for (int k = 0; k < K; ++k)
 #pragma unroll
-                                for (int j = b; j < b + kGroupEnt; ++j) {
-                                    cf[j] = he[e0 + j].c;
-                                    load_at<S, NE, LPR>(v + he[e0 + j].row0 * int64_t(Ly::RB) + own, g[j]);
-                                }
+                            for (int j = 0; j < HB; ++j) {
+                                const uint64_t t = he[size_t(k) * stride + e0 + j];
+                                cf[k][j] = hc[uint32_t(t >> 48)];
+                                load_at<S, NE, LPR>(phase(v + ((t << 16) >> (16 - LOGB))) + own, g[k][j]);
                             }
 #pragma unroll
-                        for (int b = 0; b < HB; b += kGroupEnt)
-                            if (b == 0 || e0 + b < n) {
+                        for (int k = 0; k < K; ++k)
 #pragma unroll
-                                for (int j = b; j < b + kGroupEnt; ++j)
+                            for (int j = 0; j < HB; ++j)
 #pragma unroll
-                                    for (int e = 0; e < NE; ++e) acc[k][e] += cf[j] * double(g[j][e]);
-                            }
+                                for (int e = 0; e < NE; ++e) acc[k][e] += cf[k][j] * double(g[k][j][e]);
                     }
                 }
 
@@ -242,7 +258,7 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
                 }
                 uint32_t ex[OB];
 #pragma unroll
-                for (int j = 0; j < OB; ++j) ex[j] = n_lh ? xb[size_t(lhops[j].col) * n_low] : 0u;
+                for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[j].col) * n_low];
                 for (int o = 0; o < n_lh; o += OB) {
                     // lanes of rows that are not live keep zeros, so only the
                     // loads are predicated
@@ -267,10 +283,8 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
                     uint32_t sg[OB];
 #pragma unroll
                     for (int j = 0; j < OB; ++j) sg[j] = SIGN ? (ex[j] << 1) & 0x80000000u : 0u;
-                    if (o + OB < n_lh) {
 #pragma unroll
-                        for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[o + OB + j].col) * n_low];
-                    }
+                    for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[o + OB + j].col) * n_low];   // padded
 #pragma unroll
                     for (int j = 0; j < OB; ++j) {
                         const double c = lhops[o + j].c;

@@ -341,16 +341,16 @@ extern "C" int hphi_ham_build(const hphi_basis* basis, const hphi_term* terms, i
     const size_t n_low = size_t(1) << basis->b_lo;
     const size_t n_hh = gh.hh.size(), n_lh = gh.lh.size(), n_ci = gh.ci.size(), n_ll = gh.ll.size(), n_col = gh.col.size();
     const size_t stride = (n_hh + kGroupEnt - 1) / kGroupEnt * kGroupEnt;
-    const size_t ll_rows = (n_ll + kGroupPad - 1) / kGroupPad * kGroupPad;
+    const size_t ll_rows = size_t(group_rows(int(n_ll)));
     const size_t o_ll = take(n_ll * sizeof(GLow)), o_coef = take(gh.coef.size() * 8), o_col = take(n_col * sizeof(GColumn)),
-                 o_lh = take(n_lh * sizeof(GCross)), o_ci = take(n_ci * 4), o_bhh = take(n_hh * sizeof(GBuildOp)),
+                 o_lh = take((n_lh + kGroupPad) * sizeof(GCross)), o_ci = take(n_ci * 4), o_bhh = take(n_hh * sizeof(GBuildOp)),
                  o_blh = take(n_lh * sizeof(GBuildOp)), o_dlo = take(gh.dlo.size() * sizeof(GBuildDiag)),
                  o_dhi = take(gh.dhi.size() * sizeof(GBuildDiag)), o_dx = take(gh.dx.size() * sizeof(GBuildDiag));
     const size_t up_end = off;
     const size_t o_row = take(n_slot * 8), o_hv = take(n_slot * 4), o_ne = take(n_slot * 4), o_dh = take(n_slot * 8),
-                 o_hh = take(n_slot * stride * sizeof(GEnt)), o_lhe = take(n_lh * n_slot * 8),
+                 o_hh = take(n_slot * stride * 8), o_lhe = take(n_lh * n_slot * 8),
                  o_w = take(n_ci * n_slot * sizeof(double)),
-                 o_dl = take(n_low * sizeof(double)), o_nbr = take(ll_rows * n_low * 4), o_xnb = take(n_col * n_low * 4);
+                 o_dl = take(n_low * sizeof(double)), o_nbr = take(ll_rows * n_low * 4), o_xnb = take(std::max<size_t>(n_col, 1) * n_low * 4);
     bool group = grouped;
     if (alloc_fails()) {
         hphi_ham_free(H);
@@ -422,7 +422,7 @@ extern "C" int hphi_ham_build(const hphi_basis* basis, const hphi_term* terms, i
         G.hval = reinterpret_cast<uint32_t*>(m + o_hv);
         G.n_ent = reinterpret_cast<uint32_t*>(m + o_ne);
         G.dhi_out = reinterpret_cast<double*>(m + o_dh);
-        G.hh = reinterpret_cast<GEnt*>(m + o_hh);
+        G.hh = reinterpret_cast<uint64_t*>(m + o_hh);
         G.lhe = reinterpret_cast<int64_t*>(m + o_lhe);
         G.w = reinterpret_cast<double*>(m + o_w);
         G.dlo = reinterpret_cast<double*>(m + o_dl);

@@ -151,7 +151,7 @@ struct GroupPlan;
 
 // Order of a sector basis for the class-blocked product (group.h): the valid
 // high halves in the order of their groups, the charge classes, and the groups
-// for K = 1, 2, 4 and 8 high halves per wavefront.
+// for K = 1, 2, 4 and 8 high halves per wavefront (large spaces: from K = 4).
 struct GroupBasis {
     void* mem = nullptr;
     const uint32_t* d_hord = nullptr;  // [n_slot] valid-high index of each slot
