@@ -120,3 +120,26 @@ def test_class_blocked_declines_what_it_cannot_take():
         u = hp.hphi_hv(ham, torch.from_numpy(v[:, 0].copy()).cuda()).cpu().numpy()
         ref = oh.apply_h(desc, terms, v, st)[:, 0]
         assert np.linalg.norm(u - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+@pytest.mark.parametrize("name", list(CASES))
+def test_class_blocked_reads_only_the_vector(monkeypatch, name, k):
+    """NaN on both sides of the input vector (and in the output beforehand) does not reach the result."""
+    print(f"[gpu] class-blocked stays inside {name} k={k}", flush=True)
+    monkeypatch.setenv("HPHI_GROUP_K", str(k))
+    desc, terms, st, ham = _problem(name)
+    for dt in DT.values():
+        for nvec in (1, 4):
+            pad = 4096
+            n = len(st) * nvec
+            buf = torch.full((n + 2 * pad,), float("nan"), dtype=dt, device="cuda")
+            x = torch.from_numpy(uniform_vectors(len(st), list(range(nvec)), dt.is_complex)).to(dt).cuda()
+            v = buf[pad:pad + n]
+            v.copy_(x.reshape(-1))
+            v = v.reshape(len(st), nvec) if nvec > 1 else v
+            u = hp.hphi_hv(ham, v, torch.full_like(v, float("nan")))
+            red = torch.empty(4 * nvec, dtype=torch.float64, device="cuda")
+            hp.hphi_hv(ham, v, reduce=red, write=False)
+            assert torch.isfinite(torch.view_as_real(u) if dt.is_complex else u).all() and torch.isfinite(red).all()
+            assert torch.equal(u, hp.hphi_hv(ham, x if nvec > 1 else x.reshape(-1)))
