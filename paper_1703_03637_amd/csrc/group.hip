@@ -242,7 +242,6 @@ void group_order(const hphi_basis* B, const std::vector<uint64_t>& h_val, const 
     const size_t n_high = h_val.size();
     int seg = 0;
     while (seg < 12 && seg < B->b_hi - 8 && ((B->dim * 8) >> seg) > (int64_t(96) << 20)) ++seg;
-    if (const char* e = std::getenv("HPHI_GROUP_SEG")) seg = std::min(B->b_hi, std::max(0, std::atoi(e)));
     const int shift = B->b_hi - seg;
     std::vector<int> cls_of(size_t(cls_off[size_t(ncls)]) + 1, 0);
     for (int c = 0; c < ncls; ++c)
