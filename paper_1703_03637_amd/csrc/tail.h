@@ -91,11 +91,17 @@ __device__ __forceinline__ void tail_step(const Tail& T, const double* red, int 
     }
 }
 
-// A block partial: written through to where every XCD sees it, so that no block
-// has to write its whole L2 back (a release fence at device scope does, and cost
-// 20 to 30 us per launch of a few hundred blocks)
+// A block partial, where every XCD sees it.  An exchange that returns the old
+// value has been performed at the point where the device's atomics meet once
+// the value is back, so a ticket taken after that cannot overtake it; the
+// acknowledgement of a plain write-through store does not say as much.  (A
+// release fence at device scope would do too, but writes the whole L2 back: 20
+// to 30 us per launch of a few hundred blocks.)
 __device__ __forceinline__ void put_partial(double* p, double x) {
-    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long old =
+        __hip_atomic_exchange(reinterpret_cast<unsigned long long*>(p), static_cast<unsigned long long>(__double_as_longlong(x)),
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::"v"(old));   // the value is waited for
 }
 
 __device__ __forceinline__ double get_partial(const double* p) {
@@ -110,7 +116,7 @@ __device__ __forceinline__ double get_partial(const double* p) {
 // `flag`: one word of LDS.
 __device__ __forceinline__ bool tail_last(uint32_t* tickets, int blk, int n_blocks, int* flag) {
     if (threadIdx.x < 64) {
-        // the wave's stores have arrived before its ticket counts
+        // the wave's exchanges have returned before its ticket counts
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0) {
             const int g = blk >> 5, n_g = (n_blocks + 31) >> 5;
