@@ -306,7 +306,7 @@ typedef struct {
     int32_t n_iter;        /* number of Lanczos steps (size of T_n), >= 1        */
     int32_t dtype;         /* storage type of the Lanczos vectors                */
     int32_t refine;        /* 1: second pass for the eigenvector + FP64 check    */
-    int32_t use_graph;     /* 1: replay the iteration from a captured HIP graph  */
+    int32_t use_graph;     /* 1: long runs replay a captured HIP graph of steps  */
     double breakdown_tol;  /* relative beta tolerance, <= 0 selects 1e-13        */
 } hphi_lanczos_opts;
 
@@ -333,10 +333,11 @@ typedef struct {
  * product.
  * Several problems (n_hams > 1, up to 64) that share the coefficient type,
  * the space kind (sector or full) and the configuration width run as one
- * batched recurrence: each step is one persistent product launch, one
- * update launch and one scalar launch for all of them (uneven sizes split
- * the grid in proportion to their tiles), each odd/even step pair replayed
- * from one captured graph; other combinations run one problem at a time.
+ * batched recurrence: each step is one persistent product launch and one
+ * update launch for all of them (uneven sizes split the grid in proportion
+ * to their work; the last block of each problem takes its scalars); other
+ * combinations run one problem at a time.  Runs of more than 512 steps
+ * replay a captured graph of 32 with use_graph.
  *   hams[n_hams]  one Hamiltonian per independent problem (e.g. Sz sectors)
  *   v0[h]         device start vector, storage dtype, dim_h entries
  *   work[h]       device scratch of 2 * dim_h storage elements
@@ -423,8 +424,9 @@ int hphi_tpq_step(const hphi_ham* ham, const void* psi_in, void* psi_out, int64_
  * is hphi_tpq_step with k = k0 + j reading psi_a (j even) or psi_b (j odd) and
  * writing the other, with input scale in_scale (device [nvec] or NULL = 1)
  * for j = 0 and the previous step's 1/|phi| after that.  The step index and
- * the scales stay on the device, so with use_graph the steps after the first
- * are replayed in pairs from one captured HIP graph (no host work per step).
+ * the scales stay on the device: one launch per step where the sums are few
+ * enough for its last block, and with use_graph runs of more than 512 steps
+ * replay a captured HIP graph of 32 steps.
  *   obs_log  device FP64 [n_steps][4][nvec]: entry [j][q][b] is obs[q*nvec+b]
  *            of step j as hphi_tpq_step defines it (u, <H^2>/N_s^2, beta of
  *            the step's input state; 1/|phi| of its output)

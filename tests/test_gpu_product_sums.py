@@ -83,3 +83,54 @@ def test_cg_stops_where_asked(n_iter):
     # a tolerance that the first step meets, and one that the start meets
     x = torch.from_numpy(y.copy()).cuda()
     assert hp.hphi_cg_refine(ham, x, -6.0, n_inverse=1, cg_max_iter=n_iter, cg_tol=1e3)["cg_iters"] == 0
+
+
+@pytest.mark.parametrize("n_steps", [2, 512, 513, 545])
+def test_long_runs_replay_the_same_steps(n_steps):
+    """TPQ runs around the length from which a graph of 32 steps is replayed: bit for bit the eager run."""
+    print(f"[gpu] tpq run {n_steps} steps", flush=True)
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(BasisDesc("spin", 8, "sz", two_sz=0)),
+                            [L.heisenberg_bond(i, (i + 1) % 8) for i in range(8)])
+    psi = torch.from_numpy(uniform_vectors(ham.dim, [1, 2], True)).cuda()
+    out = []
+    for graph in (True, False):
+        a, b = psi.clone(), torch.empty_like(psi)
+        log = hp.hphi_tpq_run(ham, a, b, 1.5, 1, n_steps, use_graph=graph)
+        out.append((log.clone(), (a if n_steps % 2 == 0 else b).clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    lz = [hp.hphi_lanczos([ham], [psi[:, 0].contiguous()], 20, use_graph=g)[0] for g in (True, False)]
+    assert np.array_equal(lz[0]["alpha"], lz[1]["alpha"])
+
+
+@pytest.mark.parametrize("bits", [9, 14, 17, 19])
+def test_sums_of_every_launch_are_its_own(bits):
+    """2,000 products that alternate between two inputs: every launch's sums are those of its input,
+    bit for bit (a last block that read a partial of the launch before would mix the two)."""
+    print(f"[gpu] sums of alternating products {bits} bits", flush=True)
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(BasisDesc("spin", bits)), [L.heisenberg_bond(i, (i + 1) % bits) for i in range(bits)])
+    n = 2000
+    xs = [device_uniform(ham.dim, 0, seed, False, torch.float64) for seed in (1, 2)]
+    xs[1] *= 3.0
+    log = torch.empty((n, 4), dtype=torch.float64, device="cuda")
+    for k in range(n):
+        hp.hphi_hv(ham, xs[k & 1], reduce=log[k], write=False)
+    torch.cuda.synchronize()
+    assert torch.equal(log[0::2], log[0].expand(n // 2, 4)) and torch.equal(log[1::2], log[1].expand(n // 2, 4))
+    x = xs[0].double()
+    assert abs(float(log[0, 0]) - float((x * x).sum())) <= 1e-12 * float((x * x).sum())
+
+
+def test_cg_solves_repeat_bit_for_bit():
+    """200 CG solves from fresh workspaces give the same bits."""
+    print("[gpu] repeated cg", flush=True)
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(BasisDesc("spin", 18, "sz", two_sz=0)), [L.heisenberg_bond(i, (i + 1) % 18) for i in range(18)])
+    y = device_uniform(ham.dim, 0, 4, False, torch.float64)
+    y /= torch.linalg.vector_norm(y)
+    first = None
+    for _ in range(200):
+        x = y.clone()
+        r = hp.hphi_cg_refine(ham, x, -10.0, n_inverse=1, cg_max_iter=12, cg_tol=1e-300)
+        got = (r["e_refined"], r["cg_iters"], x)
+        if first is None:
+            first = got
+        assert got[0] == first[0] and got[1] == 12 and torch.equal(x, first[2])
