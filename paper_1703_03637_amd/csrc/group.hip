@@ -216,8 +216,13 @@ bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_c
         }
         out.col.push_back(GColumn{lh[a].mi, lh[a].sm});
     }
+    // Padding is never live, so it reads nothing: its column flips and holds no
+    // bit, and bit 31 of a high half (26 bits at most) is zero.  A test in the
+    // kernel instead costs 5% where the rows are wide: 18-site Hubbard, 3.4e8
+    // rows of four complex64 79.0 -> 83.3 ms.
+    if (out.lh.size() % size_t(kGroupPad)) out.col.push_back(GColumn{0, 0});
     while (out.lh.size() % size_t(kGroupPad)) {
-        out.lh.push_back(GCross{0, 0, -1, 0, 0.0});
+        out.lh.push_back(GCross{31, int32_t(out.col.size()) - 1, -1, 0, 0.0});
         out.lh_build.push_back(GBuildOp{0, 0, 0, 0, -1, 0});
     }
     // the tables stay below half of an 8-byte vector, or small

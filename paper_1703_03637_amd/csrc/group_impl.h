@@ -270,14 +270,13 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
                         const ConstPtr<int64_t> le = (ConstPtr<int64_t>)(A.plan.lhe) + size_t(o + j) * n_slot + p0;
                         const uint32_t off = (ex[j] & kGroupRank) * uint32_t(Ly::RB) + uint32_t(sub * Ly::CB);
                         const bool bi = int32_t(ex[j]) < 0;
-                        const bool on = lhops[o + j].op >= 0;   // padding reads nothing: its rank is of no block here
 #pragma unroll
                         for (int k = 0; k < K; ++k) {
                             const int64_t t = le[k];
                             if (SIGN) neg[j][k] = uint32_t(uint64_t(t) >> 32) & 0x80000000u;
 #pragma unroll
                             for (int e = 0; e < NE; ++e) g[j][k][e] = S(0);
-                            if (on && bi != (((hv[k] >> hj) & 1u) != 0))
+                            if (bi != (((hv[k] >> hj) & 1u) != 0))
                                 load_at<S, NE, LPR>(v + (SIGN ? t & INT64_MAX : t) * int64_t(Ly::RB) + off, g[j][k]);
                         }
                     }
