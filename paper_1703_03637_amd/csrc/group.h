@@ -96,7 +96,7 @@ struct GroupPlan {
     const uint32_t* hval = nullptr;
     const uint32_t* n_ent = nullptr;
     const double* dhi = nullptr;
-    const uint64_t* hh = nullptr;    // [n_slot][hh_stride] first row of the partner block | coefficient << 48
+    const uint64_t* hh = nullptr;    // [n_slot][hh_stride] first row of the partner block | coefficient << 48 (0: padding)
     const int64_t* lhe = nullptr;    // [n_lh][n_slot] first row of the partner block | high-half sign << 63
     const double* w = nullptr;       // [n_ci][n_slot]
     const uint32_t* ci = nullptr;    // [n_ci] low bit of each cross-diagonal column; + 32: it enters as a sign
