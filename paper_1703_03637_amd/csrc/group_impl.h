@@ -91,7 +91,7 @@ constexpr int group_batch(int bytes, int size, int most) { return size >= bytes 
 // SIGN: some operator with a bit in each half carries a low-half sign.
 // Args: the kernel's arguments, or a problem's in constant memory.
 template <typename S, int NS, int LPR, int K, bool SIGN, bool EXPORT, typename Args>
-__device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk) {
+__device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int blk, const int nblk) {
     constexpr int NE = NS / LPR;
     using Ly = LaneLayout<S, NE, LPR>;
     constexpr int RPW = 64 / LPR;
@@ -388,17 +388,17 @@ __device__ __forceinline__ void hvg_body(Args& A, const int blk, const int nblk)
 #pragma unroll
             for (int w = 0; w < kWavesPerBlock; ++w) s += sh[w][qi][L];
         }
-        put_partial(&A.partials[size_t(blk) * size_t(kNQ * B) + threadIdx.x], s);
+        put_partial(A.tail.mode, &A.partials[size_t(blk) * size_t(kNQ * B) + threadIdx.x], s);
     }
     if (A.tail.mode != kTailNone) {
         __syncthreads();   // the block sums are read
-        product_tail(*(const Tail*)&A.tail, A.partials, blk, nblk, B, &sh[0][0][0]);
+        product_tail(tail, A.partials, blk, nblk, B, &sh[0][0][0]);
     }
 }
 
 template <typename S, int NS, int LPR, int K, bool SIGN, bool EXPORT>
 __global__ __launch_bounds__(kBlock) void hvg_kernel(HvgArgs A) {
-    hvg_body<S, NS, LPR, K, SIGN, EXPORT>(A, int(blockIdx.x), int(gridDim.x));
+    hvg_body<S, NS, LPR, K, SIGN, EXPORT>(A, kernel_tail<HvgArgs>(), int(blockIdx.x), int(gridDim.x));
 }
 
 typedef const __attribute__((address_space(4))) HvgArgs ConstArgs;
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(kBlock) void hvg_multi_kernel(const HvgArgs* __rest
         if (int(blockIdx.x) >= begin[q]) p = q;
     p = wave_uniform(p);
     ConstArgs& A = ((ConstArgs*)(probs))[p];
-    hvg_body<S, NS, 1, K, SIGN, false>(A, int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
+    hvg_body<S, NS, 1, K, SIGN, false>(A, &A.tail, int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
 }
 
 template <typename Kernel>
@@ -431,7 +431,7 @@ int launch_hvg_k(HvgArgs& A, const HvLaunch& L, int per_cu_cap, int cus, hipStre
     for (int x = 0; x < 8; ++x) g = std::max<int64_t>(g, (int64_t(A.grp.items[x]) * LPR + kWavesPerBlock - 1) / kWavesPerBlock);
     g = std::min<int64_t>(std::max<int64_t>(g, 1) * 8, int64_t(per_cu) * cus / 8 * 8);
     g = std::min<int64_t>(g, kMaxGrid);
-    A.tail = product_tail_of(L, int(g));
+    A.tail = product_tail_of(L, int(g), kSumsMax);
     hvg_kernel<S, NS, LPR, K, SIGN, EX><<<int(g), kBlock, 0, st>>>(A);
     *grid_out = int(g);
     return check_hip(hipGetLastError(), "hvg_kernel launch");

@@ -289,9 +289,17 @@ int launch_cg_init(CgScalars* c, const double* rr, double tol, int n_max, hipStr
 // x += alpha p, r -= alpha q, |r|^2 with the stop test and beta, then p = r + beta p
 int launch_cg_update(double* x, double* r, double* p, const double* q, int64_t n, CgScalars* c, double* partials,
                      uint32_t* tickets, hipStream_t st);
-// The last block of the product takes the sums where they are few; more of
-// them are summed faster by a launch of one block per sum.
-constexpr int kTailMax = 16384;
+// The last block of a product takes the sums where the partials (blocks x
+// kNQ x nvec) are few; more of them are summed faster by a launch of one block
+// per sum.  With a scalar step to take it saves two launches and pays up to
+// kTailMax (20 steps of 184,756 complex128 rows 426 -> 385 us, 8,192 partials;
+// 65,536 partials lose 4 to 6 us a step).  Plain sums save one launch, worth 2 us
+// where the kernel is shorter than the two launches, and cost 1 to 1.5 us where it
+// is longer: the windowed and the class-blocked kernel gain up to 4,096 partials
+// (4,900 rows x 4 complex64 12.0 -> 9.8 us; 16,384 partials, 184,756 rows 23.6 -> 24.3),
+// the per-tile kernel, whose tiles take longer, up to 1,024 (1,024: 12,870 complex
+// rows 11.5 -> 11.0 us; 2,048: 13.4 -> 14.1).
+constexpr int kTailMax = 16384, kSumsMax = 4096, kSumsMaxTiles = 1024;
 struct HvLaunch {
     const hphi_ham* ham;
     const void* v;
@@ -399,8 +407,9 @@ std::vector<int> deal_blocks(const std::vector<int64_t>& items, int64_t groups);
 // the sums of a product from its block partials
 // the tail of a product of n_blocks blocks: what the kernel takes along, and
 // the launches that follow if it takes nothing
-Tail product_tail_of(const HvLaunch& L, int n_blocks);
-int launch_product_tail(const HvLaunch& L, int n_blocks, hipStream_t st);
+// (sums_max: partials up to which plain sums stay in the kernel)
+Tail product_tail_of(const HvLaunch& L, int n_blocks, int sums_max);
+int launch_product_tail(const HvLaunch& L, int n_blocks, int sums_max, hipStream_t st);
 int hv_multi_launch(const MultiPlan& P, hipStream_t st);
 // the class-blocked product when the Hamiltonian has its tables and the
 // schedule asks for it; 1 if not

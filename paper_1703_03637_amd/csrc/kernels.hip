@@ -368,7 +368,7 @@ constexpr size_t kLdsStageBytes = 64 * 1024;
 // per row in the export range and operator slot o, the target index and the
 // signed element are recorded; the diagonal sum goes to the row's pass-0 slot.
 template <typename S, bool CPLX, bool CCOEF, bool SECTOR, int B, int LPR, bool W64, int TAB, bool EXPORT = false>
-__device__ __forceinline__ void hv_body(const HvArgs& A, const int blk, const int nblk) {
+__device__ __forceinline__ void hv_body(const HvArgs& A, const TailAt tail, const int blk, const int nblk) {
     using ST = typename StateT<W64>::type;
     constexpr int NC = CPLX ? 2 : 1;
     constexpr int VPL = B / LPR;          // vectors per lane
@@ -378,6 +378,8 @@ __device__ __forceinline__ void hv_body(const HvArgs& A, const int blk, const in
     constexpr int LOGL = Log2<LPR>::value;
     static_assert(VPL * LPR == B, "LPR must divide B");
     if (A.stop && *A.stop) return;
+    __shared__ TailKeep keep;   // 32 bytes: dynamic LDS behind it stays aligned
+    keep.put(tail, A.partials, A.tail.mode, blk, nblk);
 
     const int lane = threadIdx.x & 63;
     const int sub = lane & (LPR - 1);      // which share of the vectors
@@ -706,25 +708,21 @@ __device__ __forceinline__ void hv_body(const HvArgs& A, const int blk, const in
 #pragma unroll
     for (int k = 0; k < kNQ; ++k) sh[wave][k][lane] = wq[k];
     __syncthreads();
+    double acc = 0.0;
     if (int(threadIdx.x) < kNQ * B) {
         const int k = threadIdx.x / B, b = threadIdx.x % B;
         int bsub = 0, bi = 0;
         vec_lane<S, NE, LPR, NC>(b, bsub, bi);
         const int L = (bi << (6 - LOGV)) | bsub;
-        double acc = 0.0;
 #pragma unroll
         for (int w = 0; w < kWavesPerBlock; ++w) acc += sh[w][k][L];
-        put_partial(&A.partials[size_t(blk) * (kNQ * B) + threadIdx.x], acc);
     }
-    if (A.tail.mode != kTailNone) {
-        __syncthreads();   // the block sums are read
-        product_tail(A.tail, A.partials, blk, nblk, B, &sh[0][0][0]);
-    }
+    product_end(keep, acc, B, &sh[0][0][0]);
 }
 
 template <typename S, bool CPLX, bool CCOEF, bool SECTOR, int B, int LPR, bool W64, int TAB, bool EXPORT>
 __global__ __launch_bounds__(kBlock) void hv_kernel(HvArgs A) {
-    hv_body<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB, EXPORT>(A, int(blockIdx.x), int(gridDim.x));
+    hv_body<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB, EXPORT>(A, kernel_tail<HvArgs>(), int(blockIdx.x), int(gridDim.x));
 }
 
 // Several problems in one launch (uneven sector sizes): problem p owns the
@@ -737,7 +735,8 @@ __global__ __launch_bounds__(kBlock) void hv_multi_kernel(const HvArgs* __restri
     for (int q = 1; q < n_probs; ++q)
         if (int(blockIdx.x) >= begin[q]) p = q;
     const HvArgs A = probs[p];
-    hv_body<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB>(A, int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
+    hv_body<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB>(A, (TailAt)(&probs[p].tail), int(blockIdx.x) - begin[p],
+                                                      begin[p + 1] - begin[p]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1071,6 +1070,8 @@ __global__ __launch_bounds__(kBlock) void hvw_kernel(HvwArgs A) {
     constexpr int LOGT = TL ? 6 : LOGR;
     static_assert(VPL * LPR == B, "LPR must divide B");
     if (A.stop && *A.stop) return;
+    __shared__ TailKeep keep;   // 32 bytes: dynamic LDS behind it stays aligned
+    keep.put(kernel_tail<HvwArgs>(), A.partials, A.tail.mode, int(blockIdx.x), int(gridDim.x));
     const bool first = (A.mode & 1) != 0, last = (A.mode & 2) != 0;
 
     const int lane = threadIdx.x & 63;
@@ -1352,20 +1353,16 @@ __global__ __launch_bounds__(kBlock) void hvw_kernel(HvwArgs A) {
 #pragma unroll
     for (int k = 0; k < kNQ; ++k) sh[wave][k][lane] = wq[k];
     __syncthreads();
+    double acc = 0.0;
     if (int(threadIdx.x) < kNQ * B) {
         const int k = threadIdx.x / B, b = threadIdx.x % B;
         int bsub = 0, bi = 0;
         vec_lane<S, NE, LPR, NC>(b, bsub, bi);
         const int L = (bi << (6 - LOGV)) | bsub;
-        double acc = 0.0;
 #pragma unroll
         for (int w = 0; w < kWavesPerBlock; ++w) acc += sh[w][k][L];
-        put_partial(&A.partials[size_t(blockIdx.x) * (kNQ * B) + threadIdx.x], acc);
     }
-    if (A.tail.mode != kTailNone) {
-        __syncthreads();   // the block sums are read
-        product_tail(A.tail, A.partials, int(blockIdx.x), int(gridDim.x), B, &sh[0][0][0]);
-    }
+    product_end(keep, acc, B, &sh[0][0][0]);
 }
 
 // ---- dense-block (CMA) product.  Stage c: for every block of D = 2^M rows
@@ -1856,9 +1853,10 @@ __global__ void lz_init_kernel(LzScalars* sc, const double* red, double tol, int
 // ------------------------------------------------------------------ launchers
 
 // what a product kernel of n_blocks blocks takes along
-Tail product_tail_of(const HvLaunch& L, int n_blocks) {
+Tail product_tail_of(const HvLaunch& L, int n_blocks, int sums_max) {
     Tail T = L.tail;
-    if (L.ex || T.mode == kTailNone || n_blocks * kNQ * L.nvec > kTailMax) T.mode = kTailNone;
+    const int most = T.mode == kTailSums ? sums_max : kTailMax;
+    if (L.ex || n_blocks * kNQ * L.nvec > most) T.mode = kTailNone;
     if (!T.tickets) T.tickets = L.ham->d_tickets;
     T.flag = L.ham->d_flag;
     return T;
@@ -1876,8 +1874,8 @@ static int launch_separate_tail(const HvLaunch& L, int n_blocks, hipStream_t st)
     return check_hip(hipGetLastError(), "product tail launch");
 }
 
-int launch_product_tail(const HvLaunch& L, int n_blocks, hipStream_t st) {
-    if (L.ex || product_tail_of(L, n_blocks).mode != kTailNone) return HPHI_OK;
+int launch_product_tail(const HvLaunch& L, int n_blocks, int sums_max, hipStream_t st) {
+    if (L.ex || product_tail_of(L, n_blocks, sums_max).mode != kTailNone) return HPHI_OK;
     return launch_separate_tail(L, n_blocks, st);
 }
 
@@ -1963,7 +1961,7 @@ static int launch_hv_g(const HvLaunch& L, const Schedule& sc, size_t lds, hipStr
     A.b = L.b;
     A.stop = L.stop;
     A.partials = H->d_partials;
-    A.tail = product_tail_of(L, grid);
+    A.tail = product_tail_of(L, grid, kSumsMaxTiles);
     if constexpr (EX) A.ex = *L.ex;
     if constexpr (TAB == 3) {
         const hphi_basis* Bs = H->basis;
@@ -1977,7 +1975,7 @@ static int launch_hv_g(const HvLaunch& L, const Schedule& sc, size_t lds, hipStr
     hv_kernel<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB, EX><<<grid, kBlock, lds, st>>>(A);
     int rc = check_hip(hipGetLastError(), "hv_kernel launch");
     if (rc) return rc;
-    return launch_product_tail(L, grid, st);
+    return launch_product_tail(L, grid, kSumsMaxTiles, st);
 }
 
 // Table placement: 0 = pattern table and low rank table in LDS, 1 = both read
@@ -2155,7 +2153,7 @@ static int launch_hvw_t(const HvLaunch& L, const PassPlan* P, const Schedule& sc
     A.b = L.b;
     A.stop = L.stop;
     A.partials = H->d_partials;
-    A.tail = product_tail_of(L, grid);
+    A.tail = product_tail_of(L, grid, kSumsMax);
     if constexpr (EX) {
         A.ex = *L.ex;
         if (P->n_pass > A.ex.n_pass) return set_error(HPHI_EINVAL, "element export: too many passes in the plan");
@@ -2179,7 +2177,7 @@ static int launch_hvw_t(const HvLaunch& L, const PassPlan* P, const Schedule& sc
         int rc = check_hip(hipGetLastError(), "hvw_kernel launch");
         if (rc) return rc;
     }
-    return launch_product_tail(L, grid, st);
+    return launch_product_tail(L, grid, kSumsMax, st);
 }
 
 template <typename S, bool CPLX, bool CCOEF, int B, bool EX>

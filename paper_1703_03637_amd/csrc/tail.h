@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+
 #include "hphi_internal.h"
 
 namespace hphi {
@@ -104,6 +106,12 @@ __device__ __forceinline__ void put_partial(double* p, double x) {
     asm volatile("" ::"v"(old));   // the value is waited for
 }
 
+// the same for a kernel that may leave the sums to a later launch
+__device__ __forceinline__ void put_partial(int32_t mode, double* p, double x) {
+    if (mode == kTailNone) *p = x;
+    else put_partial(p, x);
+}
+
 __device__ __forceinline__ double get_partial(const double* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -157,10 +165,50 @@ __device__ __forceinline__ void tail_sums(const double* partials, int n_parts, i
     }
 }
 
-// The tail of a product over nvec vectors.  `lds`: 257 doubles of LDS that no
-// thread of the block reads any more.
-__device__ __forceinline__ void product_tail(const Tail& T, const double* partials, int blk, int n_blocks, int nvec, double* lds) {
-    if (T.mode == kTailNone) return;
+// Where a kernel finds its Tail.  Read as an ordinary argument it is loaded when
+// the kernel starts, and its 22 words stay in scalar registers beside the loop,
+// which spills 16 to 37 of its own for them.  The address alone costs waves too: a
+// SIMD holds 7 of a kernel of at most 96 scalar registers and 6 of more (the runtime's
+// occupancy counts 7 for both, and the persistent grid then ends in a nearly empty
+// wave: 3,312,400 rows of 2 FP64, per-tile kernel, 264 us at 96 registers, 417 at 100).
+// So block-wide LDS keeps the address until the sums are due.
+typedef const __attribute__((address_space(4))) Tail* TailAt;
+
+// of a kernel whose first argument is an Args by value
+template <typename Args>
+__device__ __forceinline__ TailAt kernel_tail() {
+    typedef const __attribute__((address_space(4))) char* Bytes;
+    return (TailAt)((Bytes)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Args, tail));
+}
+
+// What the end of a product kernel needs, in LDS: written when the kernel starts,
+// read after a barrier
+struct TailKeep {
+    uint32_t at[2], partials[2];
+    int32_t mode, n_blocks, blk, pad;
+
+    __device__ __forceinline__ void put(TailAt a, double* p, int32_t m, int b, int nb) {
+        if (threadIdx.x != 0) return;
+        at[0] = uint32_t(uint64_t(a));
+        at[1] = uint32_t(uint64_t(a) >> 32);
+        partials[0] = uint32_t(uint64_t(p));
+        partials[1] = uint32_t(uint64_t(p) >> 32);
+        mode = m;
+        n_blocks = nb;
+        blk = b;
+    }
+    __device__ __forceinline__ static uint64_t wide(const uint32_t (&w)[2]) {
+        const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int32_t(w[0])));
+        const uint32_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int32_t(w[1])));
+        return (uint64_t(hi) << 32) | lo;
+    }
+};
+
+// The tail of a product over nvec vectors (not called with kTailNone).  `lds`:
+// 257 doubles of LDS that no thread of the block reads any more.
+__device__ __forceinline__ void product_tail(TailAt at, const double* partials, int blk, int n_blocks, int nvec, double* lds) {
+    asm volatile("" : "+s"(at));   // its loads stay behind this point
+    const Tail& T = *(const Tail*)at;
     if (!tail_last(T.tickets, blk, n_blocks, reinterpret_cast<int*>(lds + 256))) return;
     const int nq = kNQ * nvec, t = int(threadIdx.x);
     tail_sums(partials, n_blocks, nq, lds);
@@ -169,6 +217,22 @@ __device__ __forceinline__ void product_tail(const Tail& T, const double* partia
         if (T.flag && !isfinite(lds[t])) atomicOr(T.flag, HPHI_NONFINITE_PRODUCT);
     }
     tail_step(T, lds, nvec);
+}
+
+// The end of a product kernel: the block's sum s of quantity and vector
+// threadIdx.x < kNQ * nvec, and the tail if it is taken along.  The block sums
+// in `lds` are read after a barrier.
+__device__ __forceinline__ void product_end(const TailKeep& keep, double s, int nvec, double* lds) {
+    const int32_t mode = __builtin_amdgcn_readfirstlane(keep.mode), blk = __builtin_amdgcn_readfirstlane(keep.blk);
+    double* const partials = reinterpret_cast<double*>(TailKeep::wide(keep.partials));
+    if (int(threadIdx.x) < kNQ * nvec) {
+        double* const p = partials + size_t(blk) * size_t(kNQ * nvec) + threadIdx.x;
+        if (mode == kTailNone) *p = s;
+        else put_partial(p, s);
+    }
+    if (mode == kTailNone) return;
+    __syncthreads();   // the block sums are read
+    product_tail(TailAt(TailKeep::wide(keep.at)), partials, blk, __builtin_amdgcn_readfirstlane(keep.n_blocks), nvec, lds);
 }
 
 // The tail of a Lanczos update: |y|^2, then beta and the next scales
