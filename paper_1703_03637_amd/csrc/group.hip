@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include "group.h"
@@ -10,8 +11,10 @@
 
 namespace hphi {
 
-int launch_hvg_f32(HvgArgs& A, const HvLaunch& L, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
-int launch_hvg_f64(HvgArgs& A, const HvLaunch& L, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g);
+int launch_hvg_f32(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, bool ex, int cap, int cus, hipStream_t st,
+                   int* g);
+int launch_hvg_f64(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, bool ex, int cap, int cus, hipStream_t st,
+                   int* g);
 int launch_hvg_multi_f32(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
                          hipStream_t st);
 int launch_hvg_multi_f64(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
@@ -285,6 +288,7 @@ void group_order(const hphi_basis* B, const std::vector<uint64_t>& h_val, const 
         a = b;
     }
     gb.n_slot = uint32_t(hord.size());
+    for (const Run& r : runs) gb.n_item += int64_t(r.n) * cls[r.cls].n_tile;
     auto put = [&](const void* src, size_t bytes) {
         const size_t o = image.size();
         image.resize(o + (bytes + 255) / 256 * 256);
@@ -325,19 +329,66 @@ int group_build(const hphi_basis* B, const GroupBuild& G) {
     return rc ? rc : check_hip(hipStreamSynchronize(nullptr), "hphi_ham_build: sector tables");
 }
 
-// High halves per wavefront.  More of them share one decode and put more
-// gathers in flight, but leave fewer wavefronts: 4,900 rows of 16 complex128
-// vectors take 20 us at K = 1 and 24 at 2, 853,776 complex128 rows (24 Lanczos
-// steps twice) 4.5, 3.8, 3.5 and 3.8 ms at 1, 2, 4 and 8, 20,058,300 FP64 rows
-// 1.03, 0.63, 0.59 and 0.58 ms, 1.25e9 FP32 rows 75, 69, 57 and 36 ms.  Rows of
-// more than two scalars hold K = 4 without spilling registers, not 8.
-static int group_k(int ns, int dtype, int64_t rows) {
+// High halves per wavefront and lanes per row, from the wavefronts there are at
+// one high half each (items of a tile of at most 64 low halves, times the lanes
+// per row): more high halves share one decode and put more gathers in flight,
+// but leave fewer wavefronts for the 1,024 SIMDs.  Microseconds at K = 1 / 2 / 4 / 8:
+//   rows of one or two scalars: 48,620 FP32 rows (932 wavefronts) 14 / 19 / 23 / 33;
+//     46,376 (3,693) 14.8 / 13.9 / 16.4 / 20; 376,740 (11,142) 22.5 / 18.4 / 17.1 /
+//     20.6; from 4,194,304 rows on 8: 20,058,300 FP64 rows 1,030 / 630 / 590 / 570
+//   rows of four: 48,620 complex128 x 2 20 / 24 / 34; 376,740 39 / 35 / 31; 853,776
+//     (15,196 wavefronts) 76 / 72 / 83; 2,704,156 133 / 126 / 131
+//   wider rows: 63,504 complex64 x 8 (5,696) 25 / 19.5 / 26; 376,740 x 4 (22,284)
+//     51 / 47 / 40; 184,756 x 4 (6,560) 23.6 / 24.6 / 20.3
+// FP64 rows of 8 or 16 scalars have twice the lanes between 3,072 and 16,384
+// items, where four high halves leave a SIMD a wavefront or two of them (352,716
+// rows of 8 FP64 104 -> 79 us in the triangular, 72 -> 59 in the kagome lattice;
+// above, 2,035,800 rows lose, 439 -> 473 us).
+struct GroupShape {
+    int k, lanes;
+};
+
+static GroupShape group_shape(int ns, bool f64, int64_t items, bool large) {
+    GroupShape s{1, group_lanes(ns)};
+    const int64_t waves = items * s.lanes;
     if (const char* e = std::getenv("HPHI_GROUP_K")) {
         const int k = std::atoi(e);
-        if (((k == 1 || k == 2) && rows < kGroupLarge) || k == 4 || (k == 8 && ns <= 2)) return k;
+        if (((k == 1 || k == 2) && !large) || k == 4 || (k == 8 && ns <= 2)) {
+            s.k = k;
+            return s;
+        }
     }
-    if (rows >= kGroupLarge) return ns <= 2 ? 8 : 4;
-    return rows >= (int64_t(1) << 19) ? 4 : rows >= (int64_t(1) << 15) ? 2 : 1;
+    if (large) s.k = ns <= 2 ? 8 : 4;
+    else if (waves < (ns == 4 ? 3200 : ns < 4 ? 3584 : 4096)) s.k = 1;
+    else if (ns <= 2) s.k = waves < 9216 ? 2 : 4;
+    else if (ns == 4) s.k = 2;
+    else if (f64 && ns <= 16 && items >= 3072 && items < 16384) s = GroupShape{4, 2 * s.lanes};
+    else s.k = waves < 6144 ? 2 : 4;
+    return s;
+}
+
+// Spaces that hold a large part of all configurations, with many operators per
+// bit: there the ascending order of the per-tile kernel keeps a partner's rows in
+// the L2 by itself, and the class order, which spreads neighbouring high halves
+// over the XCDs, re-reads wide rows (2,704,156 rows of 8 FP64, triangular lattice:
+// per tile 619 us, class-blocked 729; kagome 431 against 507; two operators fewer
+// per bit, chain: 249 against 256).  Sparser spaces, narrower rows and fewer
+// operators gain from the shared decode throughout.
+bool group_prefers_tiles(const hphi_ham* H, int nvec, int dtype) {
+    const hphi_basis* B = H->basis;
+    if (!H->grp) return false;
+    const bool f64 = dtype == HPHI_F64 || dtype == HPHI_C128;
+    const int ns = nvec * (dtype_complex(dtype) ? 2 : 1);
+    const size_t row = size_t(nvec) * dtype_size(dtype);
+    int n_off = 0;
+    for (const DevOp& o : H->ops) n_off += o.has_off ? 1 : 0;
+    const double fill = std::ldexp(double(B->dim), -B->nbits), per_bit = double(n_off) / B->nbits;
+    const int64_t items = B->grp.n_item;
+    if (f64 && row >= 64 && items >= 16384 &&
+        ((fill > 1.0 / 11 && per_bit >= 1.5 && B->dim < kGroupLarge) || (row == 64 && fill > 1.0 / 30 && per_bit >= 2.5)))
+        return true;
+    // 352,716 rows of 4 complex64, triangular lattice: 74 us per tile, 96 class-blocked
+    return !f64 && ns == 8 && fill > 1.0 / 11 && per_bit >= 2.5 && items >= 3072 && items < 16384;
 }
 
 static void group_args(const hphi_ham* H, int k, bool cplx, HvgArgs& A) {
@@ -359,9 +410,9 @@ int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
     const bool cplx = dtype_complex(L.dtype), f64 = L.dtype == HPHI_F64 || L.dtype == HPHI_C128;
     if (L.ex && !cplx) return 1;
     const int ns = L.nvec * (cplx ? 2 : 1);
-    const int k = group_k(ns, L.dtype, B->dim);
+    const GroupShape g = group_shape(ns, f64, B->grp.n_item, B->dim >= kGroupLarge);
     HvgArgs A{};
-    group_args(H, k, cplx, A);
+    group_args(H, g.k, cplx, A);
     A.v = L.v;
     A.u = L.u;
     A.y = L.y;
@@ -375,8 +426,8 @@ int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
     if (L.ex) A.ex = *L.ex;
     int grid = 0;
     const bool sign = B->desc.particle == HPHI_FERMION;
-    const int rc = f64 ? launch_hvg_f64(A, L, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
-                       : launch_hvg_f32(A, L, ns, k, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
+    const int rc = f64 ? launch_hvg_f64(A, L, ns, g.k, g.lanes, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
+                       : launch_hvg_f32(A, L, ns, g.k, g.lanes, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
     return rc ? rc : launch_product_tail(L, grid, kSumsMax, st);
 }
 
@@ -391,9 +442,12 @@ int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     MultiPlan P;
     P.n = n;
     P.dtype = dtype;
-    int64_t rows = 0;
-    for (int p = 0; p < n; ++p) rows += Ls[p].ham->basis->dim;
-    P.group_k = std::max(2, group_k(ns, dtype, rows));
+    int64_t rows = 0, n_item = 0;
+    for (int p = 0; p < n; ++p) {
+        rows += Ls[p].ham->basis->dim;
+        n_item += Ls[p].ham->basis->grp.n_item;
+    }
+    P.group_k = std::max(2, group_shape(ns, f64, n_item, rows >= kGroupLarge).k);
     P.cc = false;
     std::vector<HvgArgs> args(n, HvgArgs{});
     std::vector<int64_t> items(n);

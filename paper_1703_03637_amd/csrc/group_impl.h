@@ -437,17 +437,13 @@ int launch_hvg_k(HvgArgs& A, const HvLaunch& L, int per_cu_cap, int cus, hipStre
     return check_hip(hipGetLastError(), "hvg_kernel launch");
 }
 
-// lanes per row: a lane holds at most 16 bytes of an FP32 row and 32 bytes of
-// an FP64 row, more where four lanes are not enough
-template <typename S, int NS>
-struct GroupLanes {
-    static constexpr int NE0 = NS <= 4 ? 1 : NS <= 8 ? 2 : 4;
-    static constexpr int value = NE0;
-};
-
+// `lanes` per row: group_lanes, or twice as many for FP64 rows of 8 or 16
+// scalars with four high halves (group_shape)
 template <typename S, int NS, bool SIGN, bool EX>
-int launch_hvg_ns(HvgArgs& A, const HvLaunch& L, int k, int cap, int cus, hipStream_t st, int* grid) {
-    constexpr int LPR = GroupLanes<S, NS>::value;
+int launch_hvg_ns(HvgArgs& A, const HvLaunch& L, int k, int lanes, int cap, int cus, hipStream_t st, int* grid) {
+    constexpr int LPR = group_lanes(NS);
+    if constexpr (!EX && sizeof(S) == 8 && (NS == 8 || NS == 16))
+        if (lanes == 2 * LPR && k == 4) return launch_hvg_k<S, NS, 2 * LPR, 4, SIGN, EX>(A, L, cap, cus, st, grid);
     switch (k) {
         case 1: return launch_hvg_k<S, NS, LPR, 1, SIGN, EX>(A, L, cap, cus, st, grid);
         case 2: return launch_hvg_k<S, NS, LPR, 2, SIGN, EX>(A, L, cap, cus, st, grid);
@@ -460,15 +456,15 @@ int launch_hvg_ns(HvgArgs& A, const HvLaunch& L, int k, int cap, int cus, hipStr
 }
 
 template <typename S, bool SIGN, bool EX>
-int launch_hvg_s(HvgArgs& A, const HvLaunch& L, int ns, int k, int cap, int cus, hipStream_t st, int* grid) {
+int launch_hvg_s(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, int cap, int cus, hipStream_t st, int* grid) {
     if constexpr (!EX)
-        if (ns == 1) return launch_hvg_ns<S, 1, SIGN, EX>(A, L, k, cap, cus, st, grid);
+        if (ns == 1) return launch_hvg_ns<S, 1, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
     switch (ns) {
-        case 2: return launch_hvg_ns<S, 2, SIGN, EX>(A, L, k, cap, cus, st, grid);
-        case 4: return launch_hvg_ns<S, 4, SIGN, EX>(A, L, k, cap, cus, st, grid);
-        case 8: return launch_hvg_ns<S, 8, SIGN, EX>(A, L, k, cap, cus, st, grid);
-        case 16: return launch_hvg_ns<S, 16, SIGN, EX>(A, L, k, cap, cus, st, grid);
-        case 32: return launch_hvg_ns<S, 32, SIGN, EX>(A, L, k, cap, cus, st, grid);
+        case 2: return launch_hvg_ns<S, 2, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
+        case 4: return launch_hvg_ns<S, 4, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
+        case 8: return launch_hvg_ns<S, 8, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
+        case 16: return launch_hvg_ns<S, 16, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
+        case 32: return launch_hvg_ns<S, 32, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
     }
     return set_error(HPHI_EINVAL, "class-blocked product: bad row of %d scalars", ns);
 }
@@ -497,10 +493,11 @@ int launch_hvg_multi_s(const HvgArgs* d_args, const int* d_begin, int n, int ns,
 }  // namespace
 
 #define HVG_INSTANTIATE(S, NAME, MULTI)                                                                                \
-    int NAME(HvgArgs& A, const HvLaunch& L, int ns, int k, bool sign, bool ex, int cap, int cus, hipStream_t st, int* g) {           \
-        if (ex) return launch_hvg_s<S, true, true>(A, L, ns, k, cap, cus, st, g);                                          \
-        return sign ? launch_hvg_s<S, true, false>(A, L, ns, k, cap, cus, st, g)                                           \
-                    : launch_hvg_s<S, false, false>(A, L, ns, k, cap, cus, st, g);                                         \
+    int NAME(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, bool ex, int cap, int cus,             \
+             hipStream_t st, int* g) {                                                                                 \
+        if (ex) return launch_hvg_s<S, true, true>(A, L, ns, k, lanes, cap, cus, st, g);                                \
+        return sign ? launch_hvg_s<S, true, false>(A, L, ns, k, lanes, cap, cus, st, g)                                 \
+                    : launch_hvg_s<S, false, false>(A, L, ns, k, lanes, cap, cus, st, g);                               \
     }                                                                                                                  \
     int MULTI(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,           \
               hipStream_t st) {                                                                                        \

@@ -161,6 +161,7 @@ struct GroupBasis {
     const GGroup* d_groups[4] = {};
     uint32_t begin[4][9] = {};         // groups of each XCD (with one closing entry each)
     uint32_t items[4][8] = {};         // wavefront items of each XCD
+    int64_t n_item = 0;                // wavefront items at one high half each
     size_t cls_at = 0, groups_at[4] = {};
 };
 
@@ -414,6 +415,8 @@ int hv_multi_launch(const MultiPlan& P, hipStream_t st);
 // the class-blocked product when the Hamiltonian has its tables and the
 // schedule asks for it; 1 if not
 int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st);
+// whether the default schedule leaves a Hamiltonian with tables to the per-tile kernel
+bool group_prefers_tiles(const hphi_ham* ham, int nvec, int dtype);
 // the same for several problems in one launch
 int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out);
 int group_multi_launch(const MultiPlan& P, hipStream_t st);

@@ -41,7 +41,8 @@ int env_int(const char* name, int dflt) {
 //     against 14697, 20 sites 517 against 567), and so do 8 or 16 real FP32
 //     vectors, split over lanes (x 16, 24 sites 2768 against 2863; x 8, 26 sites
 //     6240 against 6463).
-Schedule default_schedule(const hphi_basis* B, int nvec, int dtype) {
+Schedule default_schedule(const hphi_ham* H, int nvec, int dtype) {
+    const hphi_basis* B = H->basis;
     Schedule s;
     s.windowed = 1;
     s.window_kb = 2048;
@@ -59,6 +60,7 @@ Schedule default_schedule(const hphi_basis* B, int nvec, int dtype) {
     // (more waves in flight thrash the L2 on the 36-bit kagome sector)
     s.blocks_per_cu = (B->dev.sector != 0 && B->nbits > 32) ? 6 : (full && row <= 16) ? 4 : 0;
     s.nt_streams = nvec >= 8 ? 1 : 0;
+    if (group_prefers_tiles(H, nvec, dtype)) s.sector_blocks = 0;
     // overrides for experiments
     s.windowed = env_int("HPHI_WINDOWED", s.windowed);
     s.window_kb = env_int("HPHI_L2_WINDOW_KB", s.window_kb);
@@ -133,7 +135,7 @@ Schedule schedule_for(const hphi_ham* ham, int nvec, int dtype) {
         for (const auto& t : H->tuned)
             if (t.nvec == nvec && t.dtype == dtype) return t.s;
     }
-    Schedule s = default_schedule(H->basis, nvec, dtype);
+    Schedule s = default_schedule(H, nvec, dtype);
     if (getenv("HPHI_TUNE_CACHE")) {
         Schedule c;
         if (cache_lookup(signature(H, nvec, dtype), c)) s = c;

@@ -64,3 +64,96 @@ def test_infinite_entries_give_the_oracle_s_rows(monkeypatch, problem, dt, nvec,
             want[r] = h + 2.0 * v[r]
     assert np.array_equal(np.isnan(got), np.isnan(want))
     assert np.array_equal(np.isinf(got), np.isinf(want)) and np.array_equal(got[np.isinf(got)], want[np.isinf(want)])
+
+
+def _vectors(dim, nvec, dt, seed=3):
+    x = torch.from_numpy(uniform_vectors(dim, list(range(seed, seed + nvec)), dt[0] == "c")).to(DT[dt]).cuda()
+    return x if nvec > 1 else x.reshape(-1).contiguous()
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+@pytest.mark.parametrize("nvec", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("dt", list(DT))
+@pytest.mark.parametrize("problem", [CHAIN, HUBBARD], ids=["chain19", "hubbard4x2"])
+def test_every_group_size_matches_the_per_tile_kernel(monkeypatch, problem, dt, nvec, k):
+    """Each storage type, batch and number of high halves: the per-tile kernel's result up to one rounding of
+    each stored value (two of 2^-24 in FP32) and the order of an FP64 sum (1e-13), times |H||v|."""
+    print(f"[gpu] group size {k} {dt} nvec={nvec}", flush=True)
+    desc, terms = problem
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(desc), terms)
+    v = _vectors(ham.dim, nvec, dt)
+    out = []
+    for mode, group in (("2", str(k)), ("0", "")):
+        monkeypatch.setenv("HPHI_SECTOR_BLOCKS", mode)
+        monkeypatch.setenv("HPHI_GROUP_K", group)
+        out.append(hp.hphi_hv(ham, v, a=-0.4, b=0.3).cpu().numpy().reshape(ham.dim, nvec))
+    a = abs(v.cpu().numpy().reshape(ham.dim, nvec).astype(np.complex128))
+    bound = (2.0 ** -23 if dt in ("f32", "c64") else 1e-13) * (0.4 * abs(oh.sparse_h(desc, terms)) @ a + 0.3 * a)
+    assert np.all(abs(out[0] - out[1]) <= bound)
+
+
+def _torus(lx, ly, up):
+    n = lx * ly
+    return BasisDesc("spin", n, "sz", two_sz=2 * up - n), [L.heisenberg_bond(i, j) for i, j in L.triangular_bonds(lx, ly)]
+
+
+# the shapes the default chooses: twice the lanes per row (3,280 wavefront items), two high halves of
+# four scalars, one, and eight lanes per row
+@pytest.mark.parametrize("lx,ly,up", [(5, 4, 10), (5, 4, 7), (6, 3, 9), (5, 5, 5)])
+@pytest.mark.parametrize("dt,nvec", [("f64", 4), ("f64", 8), ("c128", 4), ("f64", 16), ("c128", 8), ("c64", 16), ("c128", 16), ("f32", 1)])
+def test_default_shapes_match_the_per_tile_kernel(monkeypatch, lx, ly, up, dt, nvec):
+    """The default's product and sums on sectors around the limits of the shape rule (bounds as above; sums 1e-12)."""
+    print(f"[gpu] default shape {lx}x{ly} up={up} {dt} nvec={nvec}", flush=True)
+    desc, terms = _torus(lx, ly, up)
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(desc), terms)
+    v = _vectors(ham.dim, nvec, dt)
+    out = []
+    for mode in ("2", "0"):
+        monkeypatch.setenv("HPHI_SECTOR_BLOCKS", mode)
+        red = torch.empty(4 * nvec, dtype=torch.float64, device="cuda")
+        out.append((hp.hphi_hv(ham, v, reduce=red).cpu().numpy().reshape(ham.dim, nvec), red.cpu().numpy()))
+    # every |H| element is 1/4 or 1/2, at most 3 per site each
+    bound = (2.0 ** -23 if dt in ("f32", "c64") else 1e-13) * 0.75 * 3 * lx * ly
+    assert np.max(abs(out[0][0] - out[1][0])) <= bound * float(v.abs().max())
+    assert np.all(abs(out[0][1] - out[1][1]) <= 1e-12 * (0.75 * 3 * lx * ly) ** 2 * out[1][1][:nvec].max())
+
+
+@pytest.mark.parametrize("desc_terms,dt,nvec", [
+    (_torus(5, 4, 10), "c64", 4),
+    ((BasisDesc("spin", 24, "sz", two_sz=0), [L.heisenberg_bond(i, j) for i, j in L.kagome_bonds(4, 2)]), "f64", 8),
+], ids=["triangular20_c64x4", "kagome24_f64x8"])
+def test_dense_sectors_of_wide_rows_keep_the_per_tile_kernel(monkeypatch, desc_terms, dt, nvec):
+    """Sectors that the default leaves to the per-tile kernel: its bits, and they are not the other kernel's."""
+    print(f"[gpu] dense sector {dt} nvec={nvec}", flush=True)
+    desc, terms = desc_terms
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(desc), terms)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    v = torch.empty((ham.dim, nvec), dtype=DT[dt], device="cuda")
+    (torch.view_as_real(v) if v.dtype.is_complex else v).normal_(generator=g)
+    out = {}
+    for mode in ("", "0", "2"):
+        monkeypatch.setenv("HPHI_SECTOR_BLOCKS", mode)
+        red = torch.empty(4 * nvec, dtype=torch.float64, device="cuda")
+        out[mode] = (hp.hphi_hv(ham, v, reduce=red), red)
+    assert torch.equal(out[""][0], out["0"][0]) and torch.equal(out[""][1], out["0"][1])
+    assert not torch.equal(out["2"][1], out["0"][1])
+
+
+@pytest.mark.parametrize("k", [2, 4, 8])
+@pytest.mark.parametrize("dt", ["f64", "c64"])
+def test_batched_fermion_lanczos_matches_single_problems(monkeypatch, dt, k):
+    """Several fermion sectors in one batched recurrence, at each number of high halves: alpha, beta and energies
+    of the problems run one by one (rounding of 12 steps: 1e-10 in FP64, 1e-4 in FP32 storage)."""
+    print(f"[gpu] batched fermion lanczos {dt} k={k}", flush=True)
+    monkeypatch.setenv("HPHI_GROUP_K", str(k))
+    terms = L.hubbard_terms(L.rect_bonds(4, 2), 8, t=1.0, U=8.0)
+    hams = [hp.hphi_ham_build(hp.hphi_basis_build(BasisDesc("fermion", 8, "nupndn", n_up=u, n_dn=d)), terms)
+            for u, d in ((4, 4), (3, 4), (2, 3))]
+    v = [_vectors(h.dim, 1, dt, 20 + i) for i, h in enumerate(hams)]
+    batch = hp.hphi_lanczos(hams, v, 12)
+    for h, x, b in zip(hams, v, batch):
+        one = hp.hphi_lanczos([h], [x], 12)[0]
+        tol = 1e-10 if dt == "f64" else 1e-4
+        assert np.allclose(b["alpha"], one["alpha"], rtol=0, atol=tol * 40) and np.allclose(b["beta"], one["beta"], rtol=0, atol=tol * 40)
+        assert abs(b["e0_refined"] - one["e0_refined"]) <= tol * 40
