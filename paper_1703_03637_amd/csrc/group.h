@@ -31,6 +31,9 @@ constexpr uint32_t kGroupRank = 0xFFFFFFu;   // rank bits of a list entry
 // 1,260 us in the per-tile kernel, 1,690 with four lanes, 1,085 with eight.
 constexpr int group_lanes(int ns) { return ns <= 4 ? 1 : ns <= 8 ? 2 : ns <= 16 ? 4 : 8; }
 
+// partials up to which plain sums stay in a launch of `grid` blocks
+constexpr int group_sums_max(int grid) { return grid <= 256 ? kSumsMaxShort : kSumsMax; }
+
 // one charge class of the low half
 struct GClass {
     uint32_t l_off, n_l;      // its low halves in `lows`

@@ -428,7 +428,7 @@ int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
     const bool sign = B->desc.particle == HPHI_FERMION;
     const int rc = f64 ? launch_hvg_f64(A, L, ns, g.k, g.lanes, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
                        : launch_hvg_f32(A, L, ns, g.k, g.lanes, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
-    return rc ? rc : launch_product_tail(L, grid, kSumsMax, st);
+    return rc ? rc : launch_product_tail(L, grid, group_sums_max(grid), st);
 }
 
 // Several problems that all have the class-blocked tables: the problems share

@@ -420,7 +420,7 @@ template <typename Kernel>
 int group_occupancy(Kernel k) {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, kBlock, 0) != hipSuccess || nb < 1) nb = 1;
-    return nb;
+    return std::min(nb, kScalarBlocks);
 }
 
 template <typename S, int NS, int LPR, int K, bool SIGN, bool EX>
@@ -431,7 +431,7 @@ int launch_hvg_k(HvgArgs& A, const HvLaunch& L, int per_cu_cap, int cus, hipStre
     for (int x = 0; x < 8; ++x) g = std::max<int64_t>(g, (int64_t(A.grp.items[x]) * LPR + kWavesPerBlock - 1) / kWavesPerBlock);
     g = std::min<int64_t>(std::max<int64_t>(g, 1) * 8, int64_t(per_cu) * cus / 8 * 8);
     g = std::min<int64_t>(g, kMaxGrid);
-    A.tail = product_tail_of(L, int(g), kSumsMax);
+    A.tail = product_tail_of(L, int(g), group_sums_max(int(g)));
     hvg_kernel<S, NS, LPR, K, SIGN, EX><<<int(g), kBlock, 0, st>>>(A);
     *grid_out = int(g);
     return check_hip(hipGetLastError(), "hvg_kernel launch");

@@ -300,7 +300,15 @@ int launch_cg_update(double* x, double* r, double* p, const double* q, int64_t n
 // (4,900 rows x 4 complex64 12.0 -> 9.8 us; 16,384 partials, 184,756 rows 23.6 -> 24.3),
 // the per-tile kernel, whose tiles take longer, up to 1,024 (1,024: 12,870 complex
 // rows 11.5 -> 11.0 us; 2,048: 13.4 -> 14.1).
-constexpr int kTailMax = 16384, kSumsMax = 4096, kSumsMaxTiles = 1024;
+// A class-blocked launch of at most 256 blocks, a wavefront to a SIMD, is always the
+// shorter one and gains up to kSumsMaxShort (4,900 rows x 8 complex64 12.0 -> 10.6).
+constexpr int kTailMax = 16384, kSumsMax = 4096, kSumsMaxTiles = 1024, kSumsMaxShort = 8192;
+// Blocks of 4 wavefronts that a CU holds of a kernel with more than 96 scalar
+// registers: 800 of a SIMD go to wavefronts in steps of 16, 16 more each for the
+// trap handler.  The runtime's occupancy does not count those and says 7 or 8, and
+// a persistent grid of that size ends in a nearly empty wave (3,312,400 rows of one
+// complex128, per-tile kernel: 6 blocks 291 us, 7 blocks 400).
+constexpr int kScalarBlocks = 6;
 struct HvLaunch {
     const hphi_ham* ham;
     const void* v;

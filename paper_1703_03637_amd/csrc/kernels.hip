@@ -1946,7 +1946,9 @@ static int launch_hv_g(const HvLaunch& L, const Schedule& sc, size_t lds, hipStr
     const hphi_ham* H = L.ham;
     static const int occ = occupancy_blocks(hv_kernel<S, CPLX, CCOEF, SECTOR, B, LPR, W64, TAB, EX>);
     const int64_t tiles = EX ? L.ex->t1 - L.ex->t0 : H->basis->dev.n_tiles;
-    const int grid = make_grid(occupancy_with_lds(occ, lds, TAB == 3 ? 0 : 8 * 1024), sc, tiles < 1 ? 1 : tiles);
+    int per_cu = occupancy_with_lds(occ, lds, TAB == 3 ? 0 : 8 * 1024);
+    if (SECTOR && B == 1) per_cu = std::min(per_cu, kScalarBlocks);
+    const int grid = make_grid(per_cu, sc, tiles < 1 ? 1 : tiles);
     HvArgs A;
     A.bs = H->basis->dev;
     A.ops = H->d_ops;
