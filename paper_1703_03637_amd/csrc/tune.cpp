@@ -26,13 +26,45 @@ int env_int(const char* name, int dflt) {
     return (e && *e) ? atoi(e) : dflt;
 }
 
-// Full space (microseconds per product on the Kitaev-Heisenberg honeycomb,
-// before -> after this rule replaced 3 passes of 2 MB windows everywhere):
+// How far a full-space Hamiltonian reaches: the operators that flip a bit beyond a
+// window of 2 MB of rows, and whether most operators are live in all rows (one that
+// conserves a charge is in half of them, and counts half unless most are).
+struct Reach {
+    double far = 0.0;
+    bool all_live = false;
+};
+
+Reach reach_of(const hphi_ham* H, size_t row) {
+    int w = 0;
+    while ((row << (w + 1)) <= (size_t(2) << 20)) ++w;
+    Reach r;
+    double live = 0.0;
+    int n = 0, n_far = 0;
+    for (const DevOp& o : H->ops) {
+        if (!o.has_off) continue;
+        double l = 0.0;
+        for (int q = 0; q < 4; ++q)      // one bit: only the patterns 0 and 3 occur
+            if (o.cr[q] != 0.0 || o.ci[q] != 0.0) l += o.bi != o.bj ? 0.25 : (q == 0 || q == 3) ? 0.5 : 0.0;
+        if (o.xmask >> w) {
+            r.far += l;
+            ++n_far;
+        }
+        live += l;
+        ++n;
+    }
+    r.all_live = live > 0.75 * n;
+    if (r.all_live) r.far = n_far;
+    return r;
+}
+
+// Full space (microseconds per product, this rule against three passes of 2 MB
+// windows everywhere; 16 to 26 bits, 36 Hamiltonians):
 //   rows of at most 16 bytes: one pass in natural order with four blocks per
 //     CU.  A lane holds a whole row, so a wavefront's partner rows are whole
 //     lines, and a second pass costs more than the L2 misses it saves; more
-//     rows in flight would leave the L2 (complex128, 24 sites 911 -> 627, 805
-//     with all blocks; 26 sites 3652 -> 2745; FP32, 24 sites 720 -> 522).
+//     rows in flight would leave the L2 (complex128, Kitaev-Heisenberg honeycomb
+//     of 24 sites 911 -> 627, 805 with all blocks; 26 sites 3652 -> 2745; FP32, 24
+//     sites 720 -> 522).
 //   wider rows: one windowed pass while the vector stays in the memory-side
 //     cache (64 bytes: up to 256 MB, 22 sites 662 -> 559; 128 bytes, whose
 //     window passes pay sooner: up to 32 MB, 18 sites 81 -> 75), else two
@@ -41,6 +73,17 @@ int env_int(const char* name, int dflt) {
 //     against 14697, 20 sites 517 against 567), and so do 8 or 16 real FP32
 //     vectors, split over lanes (x 16, 24 sites 2768 against 2863; x 8, 26 sites
 //     6240 against 6463).
+//   The one pass gathers the far partners from beyond the L2, so it loses where
+//     operators are live in every row and many reach far (complex128 x 2, XYZ kagome
+//     of 21 sites, 13 far: 78 -> 101; Kitaev-Heisenberg, 22 sites, 10 far: 187 -> 208),
+//     sooner the fewer bytes a lane has to gather and the larger the vector
+//     (10 far, 32 MB: still 56 -> 49 in the lattice that wraps in one direction);
+//     conserving operators, live in half of the rows, always gain (20 far of 60,
+//     triangular, 20 sites: 83 -> 76).
+//   Where they reach less far, conserving Hamiltonians take the one pass beyond the
+//     memory-side cache too (chain of 24 sites, complex128 x 2: 875, two passes 900,
+//     one 748; open Hubbard chain of 11 sites, complex64 x 16: 1004, 1070, 864).
+//   20 sites x 16 complex64 with all rows live keep three passes of 2 MB (240, 254).
 Schedule default_schedule(const hphi_ham* H, int nvec, int dtype) {
     const hphi_basis* B = H->basis;
     Schedule s;
@@ -50,10 +93,29 @@ Schedule default_schedule(const hphi_ham* H, int nvec, int dtype) {
     const size_t row = size_t(nvec) * dtype_size(dtype);
     const size_t bytes = row * size_t(B->dim);
     const bool full = B->dev.sector == 0;
-    if (full && (row <= 16 || bytes <= (size_t(row <= 64 ? 256 : 32) << 20))) s.max_passes = 1;
-    else if (full && row <= 128 && (nvec < 8 || row > 64)) {
-        s.window_kb = 1024;
-        s.max_passes = 2;
+    const bool f32 = dtype == HPHI_F32, f64 = dtype == HPHI_F64 || dtype == HPHI_C128;
+    constexpr size_t MB = size_t(1) << 20;
+    if (full && row <= 16) {
+        s.max_passes = 1;
+    } else if (full && row <= 128) {
+        const Reach r = reach_of(H, row);
+        if (bytes <= (row <= 64 ? 256 : 32) * MB) {
+            // far operators, live in every row, from which the windows pay
+            const double many = f32 || (row < 128 && bytes <= 16 * MB) ? 1e9
+                              : (row == 32 && f64) || (row == 64 && nvec == 8) ? (bytes > 64 * MB ? 7 : row == 32 ? 8 : 10)
+                              : row <= 64 ? 13 : 15;
+            if (!r.all_live || r.far < many) s.max_passes = 1;
+        } else if (nvec < 8 || row > 64) {
+            const bool cached = row == 128 && bytes <= 256 * MB;
+            if (!r.all_live && r.far <= (cached ? 9 : 8)) {
+                s.max_passes = 1;
+            } else if (!(r.all_live && row == 128 && nvec == 16 && bytes <= 128 * MB && r.far >= 10 && r.far <= 16)) {
+                s.window_kb = 1024;
+                s.max_passes = 2;
+            }
+        }
+    } else if (full && bytes <= 32 * MB) {
+        s.max_passes = 1;
     }
     s.lpr = nvec >= 16 ? 4 : (nvec >= 8 ? 2 : 1);
     // sectors wider than 32 bits: 6 resident blocks per CU measured fastest
