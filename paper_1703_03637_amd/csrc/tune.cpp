@@ -156,7 +156,12 @@ std::string signature(const hphi_ham* H, int nvec, int dtype) {
     return buf;
 }
 
-bool cache_lookup(const std::string& sig, Schedule& out) {
+// Kernels a line of the cache was chosen among: lines of sector Hamiltonians that
+// the class-blocked kernel can run count only with this mark or if they name it
+// (older ones compared the kernels before it).
+constexpr char kKernelSet[] = "k2";
+
+bool cache_lookup(const hphi_ham* H, const std::string& sig, Schedule& out) {
     const char* path = getenv("HPHI_TUNE_CACHE");
     if (!path) return false;
     FILE* f = fopen(path, "r");
@@ -164,15 +169,26 @@ bool cache_lookup(const std::string& sig, Schedule& out) {
     char line[512];
     bool found = false;
     while (fgets(line, sizeof(line), f)) {
-        char key[300];
+        // key, seven or eight integers, microseconds, mark
+        std::vector<std::string> w;
+        char* save = nullptr;
+        for (char* t = strtok_r(line, " \t\r\n", &save); t; t = strtok_r(nullptr, " \t\r\n", &save)) w.push_back(t);
+        if (w.empty() || w[0] != sig) continue;
+        const bool marked = w.back() == kKernelSet;
         Schedule s;
-        const int n = sscanf(line, "%299s %d %d %d %d %d %d %d %d", key, &s.windowed, &s.window_kb, &s.max_passes,
-                             &s.lpr, &s.blocks_per_cu, &s.stage_tables, &s.nt_streams, &s.sector_blocks);
-        if (n == 8) s.sector_blocks = 0;   // entries written before the block-staged sector kernel
-        if (n >= 8 && sig == key) {
-            out = s;   // the last entry for a key wins
-            found = true;
+        int* const field[] = {&s.windowed, &s.window_kb, &s.max_passes, &s.lpr, &s.blocks_per_cu, &s.stage_tables, &s.nt_streams,
+                              &s.sector_blocks};
+        s.sector_blocks = 0;   // seven integers: before the block-staged sector kernel
+        size_t n = 0;
+        for (char* end = nullptr; n < 8 && n + 1 < w.size(); ++n) {
+            const long x = std::strtol(w[n + 1].c_str(), &end, 10);
+            if (*end) break;
+            *field[n] = int(x);
         }
+        if (n < 7) continue;
+        if (H->grp && !marked && s.sector_blocks != 2) continue;
+        out = s;   // the last entry for a key wins
+        found = true;
     }
     fclose(f);
     return found;
@@ -183,8 +199,8 @@ void cache_store(const std::string& sig, const Schedule& s, double us) {
     if (!path) return;
     FILE* f = fopen(path, "a");
     if (!f) return;
-    fprintf(f, "%s %d %d %d %d %d %d %d %d %.2f\n", sig.c_str(), s.windowed, s.window_kb, s.max_passes, s.lpr,
-            s.blocks_per_cu, s.stage_tables, s.nt_streams, s.sector_blocks, us);
+    fprintf(f, "%s %d %d %d %d %d %d %d %d %.2f %s\n", sig.c_str(), s.windowed, s.window_kb, s.max_passes, s.lpr,
+            s.blocks_per_cu, s.stage_tables, s.nt_streams, s.sector_blocks, us, kKernelSet);
     fclose(f);
 }
 
@@ -200,7 +216,7 @@ Schedule schedule_for(const hphi_ham* ham, int nvec, int dtype) {
     Schedule s = default_schedule(H, nvec, dtype);
     if (getenv("HPHI_TUNE_CACHE")) {
         Schedule c;
-        if (cache_lookup(signature(H, nvec, dtype), c)) s = c;
+        if (cache_lookup(H, signature(H, nvec, dtype), c)) s = c;
         std::lock_guard<std::mutex> lock(H->plan_mu);
         H->tuned.push_back({nvec, dtype, s});
     }
