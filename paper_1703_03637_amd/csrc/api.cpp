@@ -71,21 +71,23 @@ static void report_progress(hipStream_t st, const char* what, int k, int n) {
     std::fflush(stderr);
 }
 
-// Run `pairs` pairs of steps; body(stream) enqueues one pair.  The steps are
-// launched one by one: with two launches per step the host stays ahead, and a
-// graph's kernels start later after one another than a stream's (16-site chain,
-// 200 Lanczos steps and the second pass: 7.5 ms launched, 8.8 ms replayed a pair
-// at a time, 8.6 ms sixteen; 24 steps 1.08 against 1.34 ms with the graph's
-// building).  Runs of kGraphMin pairs and more replay a graph of kGraphPairs on
-// a side stream joined to `st`, which frees the host for 3 to 4% of a run of
-// short steps.
-constexpr int kGraphPairs = 16, kGraphMin = 256;
+// Steps 1 .. n-1 of a run whose first step has been launched; step(stream,
+// parity) enqueues one (parity: its number's last bit).  The steps are launched
+// one by one: with two launches per step the host stays ahead, and a graph's
+// kernels start later after one another than a stream's (16-site chain, 200
+// Lanczos steps and the second pass: 7.5 ms launched, 8.8 ms replayed a pair at a
+// time, 8.6 ms sixteen; 24 steps 1.08 against 1.34 ms with the graph's building).
+// From 2 * kGraphMin steps on a graph of kGraphSteps is replayed on a side stream
+// joined to `st`, which frees the host for 3 to 4% of a run of short steps.  `what`:
+// progress lines, every N steps of the launched ones and behind the replay in
+// which a multiple of N was reached.
+constexpr int kGraphSteps = 32, kGraphMin = 256;
 
-template <typename Body>
-int run_pairs(hipStream_t st, Body body, int pairs, bool use_graph, const char* what = nullptr, int k0 = 0, int n = 0) {
+template <typename Step>
+int run_steps(hipStream_t st, Step step, int n, bool use_graph, const char* what = nullptr) {
     const int every = what ? progress_every() : 0;
-    int done = 0, rc = HPHI_OK;
-    if (use_graph && pairs >= kGraphMin) {
+    int k = 1, rc = HPHI_OK;
+    if (use_graph && (n - 1) / 2 >= kGraphMin) {
         hipStream_t cs;
         rc = check_hip(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking), "graph stream");
         if (rc) return rc;
@@ -98,26 +100,26 @@ int run_pairs(hipStream_t st, Body body, int pairs, bool use_graph, const char* 
         rc = check_hip(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "begin capture");
         if (!rc) {
             int r = HPHI_OK;
-            for (int k = 0; !r && k < kGraphPairs; ++k) r = body(cs);
+            for (int i = 0; !r && i < kGraphSteps; ++i) r = step(cs, (k + i) & 1);
             const hipError_t e = hipStreamEndCapture(cs, &g);
             rc = r ? r : check_hip(e, "end capture");
         }
         if (!rc) rc = check_hip(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0), "graph instantiate");
-        for (; !rc && done + kGraphPairs <= pairs; done += kGraphPairs) {
+        for (; !rc && k + kGraphSteps <= n; k += kGraphSteps) {
             rc = check_hip(hipGraphLaunch(ge, cs), "graph launch");
-            if (every > 0) report_progress(cs, what, k0 + 2 * (done + kGraphPairs), n);
+            if (every > 0 && (k + kGraphSteps) / every > k / every) report_progress(cs, what, k + kGraphSteps, n);
         }
         (void)hipEventRecord(ev, cs);
         (void)hipStreamWaitEvent(st, ev, 0);
+        (void)hipStreamSynchronize(cs);
         if (ge) (void)hipGraphExecDestroy(ge);
         if (g) (void)hipGraphDestroy(g);
-        (void)hipStreamSynchronize(cs);
         (void)hipStreamDestroy(cs);
         (void)hipEventDestroy(ev);
     }
-    for (; !rc && done < pairs; ++done) {
-        rc = body(st);
-        if (every > 0 && (done + 1) % ((every + 1) / 2) == 0) report_progress(st, what, k0 + 2 * (done + 1), n);
+    for (; !rc && k < n; ++k) {
+        rc = step(st, k & 1);
+        if (every > 0 && (k + 1) % every == 0) report_progress(st, what, k + 1, n);
     }
     return rc;
 }
@@ -346,15 +348,7 @@ extern "C" int hphi_tpq_run(const hphi_ham* ham, void* psi_a, void* psi_b, int64
     };
     int rc = launch_tpq_run_init(S, k0, st);
     if (!rc) rc = step(0, true, st);      // eager: allocates lazily built plans before any capture
-    int j = 1;
-    if (!rc) {
-        rc = run_pairs(st, [&](hipStream_t cs) {
-            int r = step(1, false, cs);
-            return r ? r : step(0, false, cs);
-        }, (n_steps - j) / 2, use_graph != 0);
-        j += (n_steps - j) / 2 * 2;
-    }
-    for (; !rc && j < n_steps; ++j) rc = step(j & 1, false, st);
+    if (!rc) rc = run_steps(st, [&](hipStream_t cs, int parity) { return step(parity, false, cs); }, n_steps, use_graph != 0);
     const hipError_t e = hipStreamSynchronize(st);
     (void)hipFree(S);
     return rc ? rc : check_hip(e, "hphi_tpq_run sync");
@@ -494,25 +488,11 @@ int lz_run(const hphi_ham* H, int dtype, const void* v0, void* A, void* B, LzDev
     if (rc) return rc;
     rc = lz_iteration(H, dtype, A, B, true, D, acc, grid, st);
     if (rc) return rc;
-    int k = 1;
-    const char* what = acc ? "lanczos second pass" : "lanczos";
     // the device-side step counter and stop flag make every replay advance the
     // recurrence
-    rc = run_pairs(st, [&](hipStream_t cs) {
-        int r = lz_iteration(H, dtype, B, A, false, D, acc, grid, cs);
-        return r ? r : lz_iteration(H, dtype, A, B, false, D, acc, grid, cs);
-    }, (n_max - 1) / 2, use_graph, what, 1, n_max);
-    if (rc) return rc;
-    k += (n_max - 1) / 2 * 2;
-    const int every = progress_every();
-    for (; k < n_max; ++k) {
-        void* X = (k & 1) ? B : A;
-        void* Y = (k & 1) ? A : B;
-        rc = lz_iteration(H, dtype, X, Y, false, D, acc, grid, st);
-        if (rc) return rc;
-        if (every > 0 && (k + 1) % every == 0) report_progress(st, what, k + 1, n_max);
-    }
-    return HPHI_OK;
+    return run_steps(st, [&](hipStream_t cs, int parity) {
+        return lz_iteration(H, dtype, parity ? B : A, parity ? A : B, false, D, acc, grid, cs);
+    }, n_max, use_graph, acc ? "lanczos second pass" : "lanczos");
 }
 
 // ---- batched recurrence: several problems advance together, one launch
@@ -641,15 +621,7 @@ int lzb_run(const hphi_ham* const* H, int n, int dtype, const void* const* v0, v
     BatchPlans P;
     int rc = lzb_plans(H, n, dtype, A, Bv, D, acc, n_iter, P);
     if (!rc) rc = lzb_iteration(P, 0, true, st);
-    int k = 1;
-    if (!rc && N >= 3) {
-        rc = run_pairs(st, [&](hipStream_t cs) {
-            int r = lzb_iteration(P, 1, false, cs);
-            return r ? r : lzb_iteration(P, 0, false, cs);
-        }, (N - 1) / 2, use_graph);
-        k += (N - 1) / 2 * 2;
-    }
-    for (; !rc && k < N; ++k) rc = lzb_iteration(P, k & 1, false, st);
+    if (!rc) rc = run_steps(st, [&](hipStream_t cs, int parity) { return lzb_iteration(P, parity, false, cs); }, N, use_graph);
     // plans are read by kernels still in flight: release after the stream drains
     hipError_t e = hipStreamSynchronize(st);
     P.release();
