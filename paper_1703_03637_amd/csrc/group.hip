@@ -11,9 +11,9 @@
 
 namespace hphi {
 
-int launch_hvg_f32(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, bool ex, int cap, int cus, hipStream_t st,
+int launch_hvg_f32(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, int cap, int cus, hipStream_t st,
                    int* g);
-int launch_hvg_f64(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, bool ex, int cap, int cus, hipStream_t st,
+int launch_hvg_f64(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, int cap, int cus, hipStream_t st,
                    int* g);
 int launch_hvg_multi_f32(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,
                          hipStream_t st);
@@ -113,6 +113,61 @@ __global__ __launch_bounds__(256) void group_low_kernel(GroupBuild G, BasisDev b
         const GColumn col = G.col[k];
         const uint32_t sg = uint32_t(__popc(l & col.sm) & 1) << 30, bit = (l & col.mi) ? 0x80000000u : 0u;
         G.xnb[size_t(k) * n_low + i] = bs.j_lo[l ^ col.mi] | sg | bit;
+    }
+}
+
+// Element export of the class-blocked product: the partners and elements that it
+// takes from its tables, row by row, under their operators.  A block takes whole
+// groups, and of these only the rows in the range, a row per lane.
+__global__ __launch_bounds__(kBlock) void hvg_export_kernel(HvgArgs A) {
+    const GroupPlan& P = A.plan;
+    const int64_t first = A.ex.row0, end = A.ex.row0 + A.ex.nrows;
+    for (uint32_t g = blockIdx.x; g < A.grp.begin[8]; g += gridDim.x) {
+        const GGroup grp = A.grp.groups[g];
+        const GClass cls = A.cls[grp.cls];       // (a closing entry has no slots)
+        for (uint32_t p = grp.p0; p < grp.p0 + grp.n; ++p) {
+            const int64_t row0 = P.row0[p];
+            if (row0 >= end || row0 + int64_t(cls.n_l) <= first) continue;
+            const uint32_t hval = P.hval[p];
+            // ranks of the rows in the range
+            const uint32_t r1 = uint32_t(std::min<int64_t>(cls.n_l, end - row0));
+            const uint32_t r0 = uint32_t(std::max<int64_t>(0, first - row0));
+            for (uint32_t r = r0 + blockIdx.y * kBlock + threadIdx.x; r < r1; r += gridDim.y * kBlock) {
+                const uint32_t li = cls.l_off + r, l = A.lows[li];
+                const int64_t row = row0 + int64_t(r) - first;
+                auto put = [&](int op, int64_t col, double c) {
+                    A.ex.col[size_t(row) * size_t(A.ex.n_slots) + size_t(op)] = col;
+                    A.ex.cr[size_t(row) * size_t(A.ex.n_slots) + size_t(op)] = c;
+                };
+                for (int o = 0; o < P.n_ll; ++o) {
+                    const uint32_t ent = P.nbr[size_t(o) * P.n_low + li];
+                    if (ent >> 24) put(P.ll_ops[o].op, row0 + int64_t(ent & kGroupRank), P.coef[ent >> 24]);
+                }
+                uint32_t e = 0;
+                for (int o = 0; o < P.n_hh; ++o) {
+                    const uint32_t m = uint32_t(P.hh_ops[o].m_hi), x = hval & m;
+                    if (x == 0 || x == m) continue;
+                    const uint64_t t = P.hh[size_t(p) * size_t(P.hh_stride) + e++];
+                    put(P.hh_ops[o].op, int64_t((t << 16) >> 16) + int64_t(r), P.coef[t >> 48]);
+                }
+                for (int o = 0; o < P.n_lh; ++o) {
+                    if (P.lh[o].op < 0) continue;
+                    const uint32_t ent = P.xnb[size_t(P.lh[o].col) * P.n_low + li];
+                    if ((ent >> 31) == ((hval >> P.lh[o].j) & 1u)) continue;
+                    const int64_t t = P.lhe[size_t(o) * P.n_slot + p];
+                    const bool minus = ((ent & (1u << 30)) != 0) != (t < 0);
+                    put(P.lh[o].op, (t & INT64_MAX) + int64_t(ent & kGroupRank), minus ? -P.lh[o].c : P.lh[o].c);
+                }
+                // the diagonal as the product adds it up
+                double dd = P.dlo[li] + P.dhi[p];
+                for (int i = 0; i < P.n_ci; ++i) {
+                    const uint32_t bit = P.ci[i];
+                    const double b = (l >> (bit & 31u)) & 1u ? 1.0 : ((bit & 32u) ? -1.0 : 0.0);
+                    dd += b * P.w[size_t(i) * P.n_slot + p];
+                }
+                A.ex.diag[size_t(row) * size_t(A.ex.n_pass)] = dd;
+            }
+        }
     }
 }
 
@@ -423,11 +478,17 @@ int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
     A.stop = L.stop;
     A.partials = H->d_partials;
     A.tail = L.tail;
-    if (L.ex) A.ex = *L.ex;
+    if (L.ex) {
+        A.ex = *L.ex;
+        const int64_t most = std::min<int64_t>(L.ex->nrows, A.plan.n_low);   // rows of one block in the range
+        const dim3 blocks(std::min<uint32_t>(A.grp.begin[8], 16384u), uint32_t(std::clamp<int64_t>((most + kBlock - 1) / kBlock, 1, 8)));
+        hvg_export_kernel<<<blocks, kBlock, 0, st>>>(A);
+        return check_hip(hipGetLastError(), "hvg_export launch");
+    }
     int grid = 0;
     const bool sign = B->desc.particle == HPHI_FERMION;
-    const int rc = f64 ? launch_hvg_f64(A, L, ns, g.k, g.lanes, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid)
-                       : launch_hvg_f32(A, L, ns, g.k, g.lanes, sign, L.ex != nullptr, sc.blocks_per_cu, cu_count(), st, &grid);
+    const int rc = f64 ? launch_hvg_f64(A, L, ns, g.k, g.lanes, sign, sc.blocks_per_cu, cu_count(), st, &grid)
+                       : launch_hvg_f32(A, L, ns, g.k, g.lanes, sign, sc.blocks_per_cu, cu_count(), st, &grid);
     return rc ? rc : launch_product_tail(L, grid, group_sums_max(grid), st);
 }
 

@@ -41,46 +41,6 @@ __device__ __forceinline__ T phase(T p) {
 // the same.
 __device__ __align__(256) uint32_t kGroupZeroRow[64] = {};
 
-// Element export: the partners and elements that the product takes from its
-// tables for this lane's row of each block, under their operators.
-template <int K>
-__device__ __forceinline__ void export_rows(const HvgArgs& A, uint32_t p0, uint32_t nk, uint32_t l, uint32_t li,
-                                            uint32_t r, bool live, const double (&dd)[K]) {
-    if (!live) return;
-    const GroupPlan& P = A.plan;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if (uint32_t(k) >= nk) continue;
-        const uint32_t p = p0 + uint32_t(k), hval = P.hval[p];
-        const int64_t row0 = P.row0[p], row = row0 + int64_t(r) - A.ex.row0;
-        if (row < 0 || row >= A.ex.nrows) continue;
-        auto put = [&](int op, int64_t col, double c) {
-            A.ex.col[size_t(row) * size_t(A.ex.n_slots) + size_t(op)] = col;
-            A.ex.cr[size_t(row) * size_t(A.ex.n_slots) + size_t(op)] = c;
-        };
-        for (int o = 0; o < P.n_ll; ++o) {
-            const uint32_t ent = P.nbr[size_t(o) * P.n_low + li];
-            if (ent >> 24) put(P.ll_ops[o].op, row0 + int64_t(ent & kGroupRank), P.coef[ent >> 24]);
-        }
-        uint32_t e = 0;
-        for (int o = 0; o < P.n_hh; ++o) {
-            const uint32_t m = uint32_t(P.hh_ops[o].m_hi), x = hval & m;
-            if (x == 0 || x == m) continue;
-            const uint64_t t = P.hh[size_t(p) * size_t(P.hh_stride) + e++];
-            put(P.hh_ops[o].op, int64_t((t << 16) >> 16) + int64_t(r), P.coef[t >> 48]);
-        }
-        for (int o = 0; o < P.n_lh; ++o) {
-            if (P.lh[o].op < 0) continue;
-            const uint32_t ent = P.xnb[size_t(P.lh[o].col) * P.n_low + li];
-            if ((ent >> 31) == ((hval >> P.lh[o].j) & 1u)) continue;
-            const int64_t t = P.lhe[size_t(o) * P.n_slot + p];
-            const bool minus = ((ent & (1u << 30)) != 0) != (t < 0);
-            put(P.lh[o].op, (t & INT64_MAX) + int64_t(ent & kGroupRank), minus ? -P.lh[o].c : P.lh[o].c);
-        }
-        A.ex.diag[size_t(row) * size_t(A.ex.n_pass)] = dd[k];
-    }
-}
-
 // items of `size` bytes that fill `bytes`, between 1 and `most`
 constexpr int group_batch(int bytes, int size, int most) { return size >= bytes ? 1 : bytes / size > most ? most : bytes / size; }
 
@@ -90,7 +50,7 @@ constexpr int group_batch(int bytes, int size, int most) { return size >= bytes 
 // sums fold the column pairs at the end.
 // SIGN: some operator with a bit in each half carries a low-half sign.
 // Args: the kernel's arguments, or a problem's in constant memory.
-template <typename S, int NS, int LPR, int K, bool SIGN, bool EXPORT, typename Args>
+template <typename S, int NS, int LPR, int K, bool SIGN, typename Args>
 __device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int blk, const int nblk) {
     constexpr int NE = NS / LPR;
     using Ly = LaneLayout<S, NE, LPR>;
@@ -173,138 +133,136 @@ __device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int b
 #pragma unroll
                 for (int e = 0; e < NE; ++e) acc[k][e] = 0.0;
 
-            if constexpr (!EXPORT) {
-                // ---- operators inside the low half: per operator the rank of
-                // each row's partner and its element, one entry for the K
-                // blocks.  Rows that the operator leaves alone skip the gathers.
-                const uint32_t* const nb = A.plan.nbr + li;
-                const int n_ll = A.plan.n_ll;
-                uint32_t ent[EB];
+            // ---- operators inside the low half: per operator the rank of
+            // each row's partner and its element, one entry for the K
+            // blocks.  Rows that the operator leaves alone skip the gathers.
+            const uint32_t* const nb = A.plan.nbr + li;
+            const int n_ll = A.plan.n_ll;
+            uint32_t ent[EB];
 #pragma unroll
-                for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(j) * n_low];
-                const char* vb[K];
-                {
-                    const ConstPtr<int64_t> r0 = phase((ConstPtr<int64_t>)(A.plan.row0) + p0);
+            for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(j) * n_low];
+            const char* vb[K];
+            {
+                const ConstPtr<int64_t> r0 = phase((ConstPtr<int64_t>)(A.plan.row0) + p0);
 #pragma unroll
-                    for (int k = 0; k < K; ++k) vb[k] = v + r0[k] * int64_t(Ly::RB);
+                for (int k = 0; k < K; ++k) vb[k] = v + r0[k] * int64_t(Ly::RB);
+            }
+            for (int o = 0; o < n_ll; o += EB) {
+                alignas(16) S g[EB][K][NE];
+                double cl[EB];
+                uint32_t off[EB];
+                bool act[EB];
+#pragma unroll
+                for (int j = 0; j < EB; ++j) {
+                    off[j] = (ent[j] & kGroupRank) * uint32_t(Ly::RB) + uint32_t(sub * Ly::CB);
+                    act[j] = (ent[j] >> 24) != 0u;
+                    cl[j] = coef[ent[j] >> 24];
                 }
-                for (int o = 0; o < n_ll; o += EB) {
-                    alignas(16) S g[EB][K][NE];
-                    double cl[EB];
-                    uint32_t off[EB];
-                    bool act[EB];
 #pragma unroll
-                    for (int j = 0; j < EB; ++j) {
-                        off[j] = (ent[j] & kGroupRank) * uint32_t(Ly::RB) + uint32_t(sub * Ly::CB);
-                        act[j] = (ent[j] >> 24) != 0u;
-                        cl[j] = coef[ent[j] >> 24];
+                for (int j = 0; j < EB; ++j)
+                    if (act[j]) {
+#pragma unroll
+                        for (int k = 0; k < K; ++k)
+                            load_at<S, NE, LPR>(vb[k] + off[j], g[j][k]);
                     }
 #pragma unroll
-                    for (int j = 0; j < EB; ++j)
-                        if (act[j]) {
+                for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(o + EB + j) * n_low];   // the list is padded
 #pragma unroll
-                            for (int k = 0; k < K; ++k)
-                                load_at<S, NE, LPR>(vb[k] + off[j], g[j][k]);
-                        }
-#pragma unroll
-                    for (int j = 0; j < EB; ++j) ent[j] = nb[size_t(o + EB + j) * n_low];   // the list is padded
-#pragma unroll
-                    for (int j = 0; j < EB; ++j)
-                        if (act[j]) {
-#pragma unroll
-                            for (int k = 0; k < K; ++k)
-#pragma unroll
-                                for (int e = 0; e < NE; ++e) acc[k][e] += cl[j] * double(g[j][k][e]);
-                        }
-                }
-
-                // ---- operators inside the high half: per high half a list of
-                // partner blocks, read at the row's own rank.  The K lists run
-                // together, HB entries of each at a time, to the end of the
-                // longest; past its end a list has the zero element and reads
-                // the row of zeros.  Without branches the scalar loads of a
-                // batch go out together, and the elements arrive behind the
-                // gathers.
-                {
-                    const ConstPtr<uint32_t> np = (ConstPtr<uint32_t>)(A.plan.n_ent) + p0;
-                    uint32_t n = 0;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) n = np[k] > n ? np[k] : n;
-                    const uint32_t stride = uint32_t(A.plan.hh_stride);
-                    const ConstPtr<uint64_t> he = (ConstPtr<uint64_t>)(A.plan.hh) + size_t(p0) * stride;
-                    const ConstPtr<double> hc = (ConstPtr<double>)(A.plan.coef);
-                    for (uint32_t e0 = 0; e0 < n; e0 += HB) {
-                        alignas(16) S g[K][HB][NE];
-                        double cf[K][HB];
+                for (int j = 0; j < EB; ++j)
+                    if (act[j]) {
 #pragma unroll
                         for (int k = 0; k < K; ++k)
 #pragma unroll
-                            for (int j = 0; j < HB; ++j) {
-                                const uint64_t t = he[size_t(k) * stride + e0 + j];
-                                const bool pad = (t >> 48) == 0;
-                                cf[k][j] = hc[uint32_t(t >> 48)];
-                                const char* const blk0 = pad ? reinterpret_cast<const char*>(kGroupZeroRow)
-                                                             : v + ((t << 16) >> (16 - LOGB));
-                                load_at<S, NE, LPR>(phase(blk0) + (own & (pad ? uint32_t(Ly::RB - 1) : ~0u)), g[k][j]);
-                            }
-#pragma unroll
-                        for (int k = 0; k < K; ++k)
-#pragma unroll
-                            for (int j = 0; j < HB; ++j)
-#pragma unroll
-                                for (int e = 0; e < NE; ++e) acc[k][e] += cf[k][j] * double(g[k][j][e]);
+                            for (int e = 0; e < NE; ++e) acc[k][e] += cl[j] * double(g[j][k][e]);
                     }
-                }
+            }
 
-                // ---- operators with one bit in each half: the partner's rank
-                // from the low half (one column per low bit), its block and
-                // the element from the high half; live where the bits differ
-                const uint32_t* const xb = A.plan.xnb + li;
-                const int n_lh = A.plan.n_lh;
-                uint32_t hv[K];
-                {
-                    const ConstPtr<uint32_t> hp = phase((ConstPtr<uint32_t>)(A.plan.hval) + p0);
+            // ---- operators inside the high half: per high half a list of
+            // partner blocks, read at the row's own rank.  The K lists run
+            // together, HB entries of each at a time, to the end of the
+            // longest; past its end a list has the zero element and reads
+            // the row of zeros.  Without branches the scalar loads of a
+            // batch go out together, and the elements arrive behind the
+            // gathers.
+            {
+                const ConstPtr<uint32_t> np = (ConstPtr<uint32_t>)(A.plan.n_ent) + p0;
+                uint32_t n = 0;
 #pragma unroll
-                    for (int k = 0; k < K; ++k) hv[k] = hp[k];
+                for (int k = 0; k < K; ++k) n = np[k] > n ? np[k] : n;
+                const uint32_t stride = uint32_t(A.plan.hh_stride);
+                const ConstPtr<uint64_t> he = (ConstPtr<uint64_t>)(A.plan.hh) + size_t(p0) * stride;
+                const ConstPtr<double> hc = (ConstPtr<double>)(A.plan.coef);
+                for (uint32_t e0 = 0; e0 < n; e0 += HB) {
+                    alignas(16) S g[K][HB][NE];
+                    double cf[K][HB];
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+#pragma unroll
+                        for (int j = 0; j < HB; ++j) {
+                            const uint64_t t = he[size_t(k) * stride + e0 + j];
+                            const bool pad = (t >> 48) == 0;
+                            cf[k][j] = hc[uint32_t(t >> 48)];
+                            const char* const blk0 = pad ? reinterpret_cast<const char*>(kGroupZeroRow)
+                                                         : v + ((t << 16) >> (16 - LOGB));
+                            load_at<S, NE, LPR>(phase(blk0) + (own & (pad ? uint32_t(Ly::RB - 1) : ~0u)), g[k][j]);
+                        }
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+#pragma unroll
+                        for (int j = 0; j < HB; ++j)
+#pragma unroll
+                            for (int e = 0; e < NE; ++e) acc[k][e] += cf[k][j] * double(g[k][j][e]);
                 }
-                uint32_t ex[OB];
+            }
+
+            // ---- operators with one bit in each half: the partner's rank
+            // from the low half (one column per low bit), its block and
+            // the element from the high half; live where the bits differ
+            const uint32_t* const xb = A.plan.xnb + li;
+            const int n_lh = A.plan.n_lh;
+            uint32_t hv[K];
+            {
+                const ConstPtr<uint32_t> hp = phase((ConstPtr<uint32_t>)(A.plan.hval) + p0);
 #pragma unroll
-                for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[j].col) * n_low];
-                for (int o = 0; o < n_lh; o += OB) {
-                    // lanes of rows that are not live keep zeros, so only the
-                    // loads are predicated
-                    alignas(16) S g[OB][K][NE];
-                    uint32_t neg[OB][K];
+                for (int k = 0; k < K; ++k) hv[k] = hp[k];
+            }
+            uint32_t ex[OB];
 #pragma unroll
-                    for (int j = 0; j < OB; ++j) {
-                        const int hj = lhops[o + j].j;
-                        const ConstPtr<int64_t> le = (ConstPtr<int64_t>)(A.plan.lhe) + size_t(o + j) * n_slot + p0;
-                        const uint32_t off = (ex[j] & kGroupRank) * uint32_t(Ly::RB) + uint32_t(sub * Ly::CB);
-                        const bool bi = int32_t(ex[j]) < 0;
+            for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[j].col) * n_low];
+            for (int o = 0; o < n_lh; o += OB) {
+                // lanes of rows that are not live keep zeros, so only the
+                // loads are predicated
+                alignas(16) S g[OB][K][NE];
+                uint32_t neg[OB][K];
 #pragma unroll
-                        for (int k = 0; k < K; ++k) {
-                            const int64_t t = le[k];
-                            if (SIGN) neg[j][k] = uint32_t(uint64_t(t) >> 32) & 0x80000000u;
+                for (int j = 0; j < OB; ++j) {
+                    const int hj = lhops[o + j].j;
+                    const ConstPtr<int64_t> le = (ConstPtr<int64_t>)(A.plan.lhe) + size_t(o + j) * n_slot + p0;
+                    const uint32_t off = (ex[j] & kGroupRank) * uint32_t(Ly::RB) + uint32_t(sub * Ly::CB);
+                    const bool bi = int32_t(ex[j]) < 0;
 #pragma unroll
-                            for (int e = 0; e < NE; ++e) g[j][k][e] = S(0);
-                            if (bi != (((hv[k] >> hj) & 1u) != 0))
-                                load_at<S, NE, LPR>(v + (SIGN ? t & INT64_MAX : t) * int64_t(Ly::RB) + off, g[j][k]);
-                        }
+                    for (int k = 0; k < K; ++k) {
+                        const int64_t t = le[k];
+                        if (SIGN) neg[j][k] = uint32_t(uint64_t(t) >> 32) & 0x80000000u;
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) g[j][k][e] = S(0);
+                        if (bi != (((hv[k] >> hj) & 1u) != 0))
+                            load_at<S, NE, LPR>(v + (SIGN ? t & INT64_MAX : t) * int64_t(Ly::RB) + off, g[j][k]);
                     }
-                    uint32_t sg[OB];
+                }
+                uint32_t sg[OB];
 #pragma unroll
-                    for (int j = 0; j < OB; ++j) sg[j] = SIGN ? (ex[j] << 1) & 0x80000000u : 0u;
+                for (int j = 0; j < OB; ++j) sg[j] = SIGN ? (ex[j] << 1) & 0x80000000u : 0u;
 #pragma unroll
-                    for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[o + OB + j].col) * n_low];   // padded
+                for (int j = 0; j < OB; ++j) ex[j] = xb[size_t(lhops[o + OB + j].col) * n_low];   // padded
 #pragma unroll
-                    for (int j = 0; j < OB; ++j) {
-                        const double c = lhops[o + j].c;
+                for (int j = 0; j < OB; ++j) {
+                    const double c = lhops[o + j].c;
 #pragma unroll
-                        for (int k = 0; k < K; ++k) {
-                            const double ck = SIGN ? __hiloint2double(__double2hiint(c) ^ int(sg[j] ^ neg[j][k]), __double2loint(c)) : c;
+                    for (int k = 0; k < K; ++k) {
+                        const double ck = SIGN ? __hiloint2double(__double2hiint(c) ^ int(sg[j] ^ neg[j][k]), __double2loint(c)) : c;
 #pragma unroll
-                            for (int e = 0; e < NE; ++e) acc[k][e] += ck * double(g[j][k][e]);
-                        }
+                        for (int e = 0; e < NE; ++e) acc[k][e] += ck * double(g[j][k][e]);
                     }
                 }
             }
@@ -323,11 +281,6 @@ __device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int b
 #pragma unroll
                     for (int k = 0; k < K; ++k) dd[k] += b * wp[k];
                 }
-            }
-
-            if constexpr (EXPORT) {
-                export_rows<K>(A, p0, nk, l, li, r, valid && sub == 0, dd);
-                continue;
             }
 
             // ---- epilogue: w = a H x + b x + cy y with x = sx v, and the sums
@@ -371,7 +324,6 @@ __device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int b
             for (int qi = 0; qi < kNQ; ++qi) wq[qi] += wave_reduce_rows<double, NE, LPR>(q[qi], lane);
         }
     }
-    if constexpr (EXPORT) return;
 
     // block sums, then the columns of each vector
 #pragma unroll
@@ -396,9 +348,9 @@ __device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int b
     }
 }
 
-template <typename S, int NS, int LPR, int K, bool SIGN, bool EXPORT>
+template <typename S, int NS, int LPR, int K, bool SIGN>
 __global__ __launch_bounds__(kBlock) void hvg_kernel(HvgArgs A) {
-    hvg_body<S, NS, LPR, K, SIGN, EXPORT>(A, kernel_tail<HvgArgs>(), int(blockIdx.x), int(gridDim.x));
+    hvg_body<S, NS, LPR, K, SIGN>(A, kernel_tail<HvgArgs>(), int(blockIdx.x), int(gridDim.x));
 }
 
 typedef const __attribute__((address_space(4))) HvgArgs ConstArgs;
@@ -413,7 +365,7 @@ __global__ __launch_bounds__(kBlock) void hvg_multi_kernel(const HvgArgs* __rest
         if (int(blockIdx.x) >= begin[q]) p = q;
     p = wave_uniform(p);
     ConstArgs& A = ((ConstArgs*)(probs))[p];
-    hvg_body<S, NS, 1, K, SIGN, false>(A, &A.tail, int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
+    hvg_body<S, NS, 1, K, SIGN>(A, &A.tail, int(blockIdx.x) - begin[p], begin[p + 1] - begin[p]);
 }
 
 template <typename Kernel>
@@ -423,48 +375,47 @@ int group_occupancy(Kernel k) {
     return std::min(nb, kScalarBlocks);
 }
 
-template <typename S, int NS, int LPR, int K, bool SIGN, bool EX>
+template <typename S, int NS, int LPR, int K, bool SIGN>
 int launch_hvg_k(HvgArgs& A, const HvLaunch& L, int per_cu_cap, int cus, hipStream_t st, int* grid_out) {
-    static const int occ = group_occupancy(hvg_kernel<S, NS, LPR, K, SIGN, EX>);
+    static const int occ = group_occupancy(hvg_kernel<S, NS, LPR, K, SIGN>);
     const int per_cu = per_cu_cap > 0 && per_cu_cap < occ ? per_cu_cap : occ;
     int64_t g = 0;
     for (int x = 0; x < 8; ++x) g = std::max<int64_t>(g, (int64_t(A.grp.items[x]) * LPR + kWavesPerBlock - 1) / kWavesPerBlock);
     g = std::min<int64_t>(std::max<int64_t>(g, 1) * 8, int64_t(per_cu) * cus / 8 * 8);
     g = std::min<int64_t>(g, kMaxGrid);
     A.tail = product_tail_of(L, int(g), group_sums_max(int(g)));
-    hvg_kernel<S, NS, LPR, K, SIGN, EX><<<int(g), kBlock, 0, st>>>(A);
+    hvg_kernel<S, NS, LPR, K, SIGN><<<int(g), kBlock, 0, st>>>(A);
     *grid_out = int(g);
     return check_hip(hipGetLastError(), "hvg_kernel launch");
 }
 
 // `lanes` per row: group_lanes, or twice as many for FP64 rows of 8 or 16
 // scalars with four high halves (group_shape)
-template <typename S, int NS, bool SIGN, bool EX>
+template <typename S, int NS, bool SIGN>
 int launch_hvg_ns(HvgArgs& A, const HvLaunch& L, int k, int lanes, int cap, int cus, hipStream_t st, int* grid) {
     constexpr int LPR = group_lanes(NS);
-    if constexpr (!EX && sizeof(S) == 8 && (NS == 8 || NS == 16))
-        if (lanes == 2 * LPR && k == 4) return launch_hvg_k<S, NS, 2 * LPR, 4, SIGN, EX>(A, L, cap, cus, st, grid);
+    if constexpr (sizeof(S) == 8 && (NS == 8 || NS == 16))
+        if (lanes == 2 * LPR && k == 4) return launch_hvg_k<S, NS, 2 * LPR, 4, SIGN>(A, L, cap, cus, st, grid);
     switch (k) {
-        case 1: return launch_hvg_k<S, NS, LPR, 1, SIGN, EX>(A, L, cap, cus, st, grid);
-        case 2: return launch_hvg_k<S, NS, LPR, 2, SIGN, EX>(A, L, cap, cus, st, grid);
-        case 4: return launch_hvg_k<S, NS, LPR, 4, SIGN, EX>(A, L, cap, cus, st, grid);
+        case 1: return launch_hvg_k<S, NS, LPR, 1, SIGN>(A, L, cap, cus, st, grid);
+        case 2: return launch_hvg_k<S, NS, LPR, 2, SIGN>(A, L, cap, cus, st, grid);
+        case 4: return launch_hvg_k<S, NS, LPR, 4, SIGN>(A, L, cap, cus, st, grid);
         case 8:
-            if constexpr (NS / LPR <= 2) return launch_hvg_k<S, NS, LPR, 8, SIGN, EX>(A, L, cap, cus, st, grid);
+            if constexpr (NS / LPR <= 2) return launch_hvg_k<S, NS, LPR, 8, SIGN>(A, L, cap, cus, st, grid);
             break;
     }
     return set_error(HPHI_EINVAL, "class-blocked product: bad group size %d", k);
 }
 
-template <typename S, bool SIGN, bool EX>
+template <typename S, bool SIGN>
 int launch_hvg_s(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, int cap, int cus, hipStream_t st, int* grid) {
-    if constexpr (!EX)
-        if (ns == 1) return launch_hvg_ns<S, 1, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
     switch (ns) {
-        case 2: return launch_hvg_ns<S, 2, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
-        case 4: return launch_hvg_ns<S, 4, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
-        case 8: return launch_hvg_ns<S, 8, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
-        case 16: return launch_hvg_ns<S, 16, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
-        case 32: return launch_hvg_ns<S, 32, SIGN, EX>(A, L, k, lanes, cap, cus, st, grid);
+        case 1: return launch_hvg_ns<S, 1, SIGN>(A, L, k, lanes, cap, cus, st, grid);
+        case 2: return launch_hvg_ns<S, 2, SIGN>(A, L, k, lanes, cap, cus, st, grid);
+        case 4: return launch_hvg_ns<S, 4, SIGN>(A, L, k, lanes, cap, cus, st, grid);
+        case 8: return launch_hvg_ns<S, 8, SIGN>(A, L, k, lanes, cap, cus, st, grid);
+        case 16: return launch_hvg_ns<S, 16, SIGN>(A, L, k, lanes, cap, cus, st, grid);
+        case 32: return launch_hvg_ns<S, 32, SIGN>(A, L, k, lanes, cap, cus, st, grid);
     }
     return set_error(HPHI_EINVAL, "class-blocked product: bad row of %d scalars", ns);
 }
@@ -493,11 +444,10 @@ int launch_hvg_multi_s(const HvgArgs* d_args, const int* d_begin, int n, int ns,
 }  // namespace
 
 #define HVG_INSTANTIATE(S, NAME, MULTI)                                                                                \
-    int NAME(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, bool ex, int cap, int cus,             \
-             hipStream_t st, int* g) {                                                                                 \
-        if (ex) return launch_hvg_s<S, true, true>(A, L, ns, k, lanes, cap, cus, st, g);                                \
-        return sign ? launch_hvg_s<S, true, false>(A, L, ns, k, lanes, cap, cus, st, g)                                 \
-                    : launch_hvg_s<S, false, false>(A, L, ns, k, lanes, cap, cus, st, g);                               \
+    int NAME(HvgArgs& A, const HvLaunch& L, int ns, int k, int lanes, bool sign, int cap, int cus, hipStream_t st,      \
+             int* g) {                                                                                                 \
+        return sign ? launch_hvg_s<S, true>(A, L, ns, k, lanes, cap, cus, st, g)                                        \
+                    : launch_hvg_s<S, false>(A, L, ns, k, lanes, cap, cus, st, g);                                      \
     }                                                                                                                  \
     int MULTI(const HvgArgs* d_args, const int* d_begin, int n, int ns, int k, bool sign, int grid, int* occ,           \
               hipStream_t st) {                                                                                        \
