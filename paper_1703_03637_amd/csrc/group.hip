@@ -532,6 +532,8 @@ int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
     if (int rc = f64 ? launch_hvg_multi_f64(nullptr, nullptr, n, ns, P.group_k, P.sign, 0, &occ, nullptr)
                      : launch_hvg_multi_f32(nullptr, nullptr, n, ns, P.group_k, P.sign, 0, &occ, nullptr))
         return rc;
+    const int cap = schedule_for(Ls[0].ham, 1, dtype).blocks_per_cu;   // as for the per-tile batch: the first problem's
+    if (cap > 0 && cap < occ) occ = cap;
     const std::vector<int> begin = deal_blocks(items, int64_t(std::max(1, occ)) * cu_count() / 8);
     P.grid = begin[n];
     const size_t a_bytes = size_t(n) * sizeof(HvgArgs);

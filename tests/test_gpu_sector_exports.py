@@ -63,3 +63,20 @@ def test_windows_of_rows_are_parts_of_the_whole_list(monkeypatch, name):
     tiles = _lists(hp.hphi_ham_build(hp.hphi_basis_build(desc), terms), 0, dim)
     for a, b in zip(whole, tiles):
         assert a[0] == b[0] and a[2] == b[2] and np.allclose(a[1], b[1], rtol=0, atol=1e-13)
+
+
+def test_batched_launches_follow_the_blocks_per_cu(monkeypatch):
+    """HPHI_BLOCKS_PER_CU reaches the batched class-blocked launch: the block sums are added in another order,
+    so the last bits of alpha change, and nothing else."""
+    print("[gpu] batched lanczos, blocks per CU", flush=True)
+    terms = [L.heisenberg_bond(i, (i + 1) % 20) for i in range(20)]
+    hams = [hp.hphi_ham_build(hp.hphi_basis_build(BasisDesc("spin", 20, "sz", two_sz=m)), terms) for m in (0, 2)]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    v = [torch.empty(h.dim, dtype=torch.float64, device="cuda").normal_(generator=g) for h in hams]
+    wide = hp.hphi_lanczos(hams, v, 8, refine=False)
+    monkeypatch.setenv("HPHI_BLOCKS_PER_CU", "1")
+    narrow = hp.hphi_lanczos(hams, v, 8, refine=False)
+    for a, b in zip(wide, narrow):
+        assert np.allclose(a["alpha"], b["alpha"], rtol=0, atol=1e-11)
+    assert any(not np.array_equal(a["alpha"], b["alpha"]) for a, b in zip(wide, narrow))
