@@ -130,6 +130,17 @@ struct GroupHost {
     std::vector<uint32_t> ci;
 };
 
+// partner blocks of a high half, padded to whole batches
+inline size_t group_ent_stride(const GroupHost& g) { return (g.hh.size() + kGroupEnt - 1) / kGroupEnt * kGroupEnt; }
+
+// bytes of the tables, the padding of the lists of low halves left out: per slot the
+// first row, the configuration, the entries, the diagonal part and 8 bytes per
+// operator; per low half 8 and 4 per operator
+inline size_t group_table_bytes(size_t n_slot, size_t n_low, const GroupHost& g) {
+    return n_slot * (24 + 8 * (group_ent_stride(g) + g.lh.size() + g.ci.size())) +
+           n_low * (8 + 4 * (g.ll.size() + g.col.size()));
+}
+
 // what the table builder reads and writes (device)
 struct GroupBuild {
     const GBuildOp* op_hh;

@@ -284,9 +284,7 @@ bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_c
         out.lh_build.push_back(GBuildOp{0, 0, 0, 0, -1, 0});
     }
     // the tables stay below half of an 8-byte vector, or small
-    const size_t n_low = size_t(1) << b_lo, n_slot = size_t(B->grp.n_slot);
-    const size_t bytes = n_slot * (24 + 16 * out.hh.size() + 8 * (out.lh.size() + out.ci.size())) +
-                         n_low * (8 + 4 * (out.ll.size() + out.col.size()));
+    const size_t bytes = group_table_bytes(size_t(B->grp.n_slot), size_t(1) << b_lo, out);
     if (bytes > (size_t(16) << 20) && bytes > size_t(B->dim) * 4) return false;
     return true;
 }

@@ -340,7 +340,7 @@ extern "C" int hphi_ham_build(const hphi_basis* basis, const hphi_term* terms, i
     const size_t n_slot = size_t(basis->grp.n_slot);
     const size_t n_low = size_t(1) << basis->b_lo;
     const size_t n_hh = gh.hh.size(), n_lh = gh.lh.size(), n_ci = gh.ci.size(), n_ll = gh.ll.size(), n_col = gh.col.size();
-    const size_t stride = (n_hh + kGroupEnt - 1) / kGroupEnt * kGroupEnt;
+    const size_t stride = group_ent_stride(gh);
     const size_t ll_rows = size_t(group_rows(int(n_ll)));
     const size_t o_ll = take(n_ll * sizeof(GLow)), o_coef = take(gh.coef.size() * 8), o_col = take(n_col * sizeof(GColumn)),
                  o_lh = take((n_lh + kGroupPad) * sizeof(GCross)), o_ci = take(n_ci * 4), o_bhh = take(n_hh * sizeof(GBuildOp)),

@@ -157,3 +157,25 @@ def test_batched_fermion_lanczos_matches_single_problems(monkeypatch, dt, k):
         tol = 1e-10 if dt == "f64" else 1e-4
         assert np.allclose(b["alpha"], one["alpha"], rtol=0, atol=tol * 40) and np.allclose(b["beta"], one["beta"], rtol=0, atol=tol * 40)
         assert abs(b["e0_refined"] - one["e0_refined"]) <= tol * 40
+
+
+@pytest.mark.parametrize("two_sz,split,blocked", [(-12, 8, True), (-10, 8, False)])
+def test_tables_are_counted_as_they_are_allocated(monkeypatch, two_sz, split, blocked):
+    """26 spins with 18 high bits: the partner lists take 8 bytes per operator inside the high half, 16 MB with
+    the rest at 7 up (657,800 rows).  Counted at 16 bytes the space would be left to the per-tile kernel.  The rows
+    differ from that kernel's in the last bits only (1e-13 of sums of up to 26 elements of 0.5 and a diagonal).
+    At 8 up the tables are 27 MB, more than half of the 12 MB vector, and the per-tile kernel stays."""
+    print(f"[gpu] class-blocked table rule 2Sz={two_sz} split={split}", flush=True)
+    desc = BasisDesc("spin", 26, "sz", two_sz=two_sz, split_bits=split)
+    terms = [L.heisenberg_bond(i, (i + 1) % 26) for i in range(26)]
+    out = []
+    for blocks in (None, "0"):
+        if blocks:
+            monkeypatch.setenv("HPHI_SECTOR_BLOCKS", blocks)
+        ham = hp.hphi_ham_build(hp.hphi_basis_build(desc), terms)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(5)
+        v = torch.empty(ham.dim, dtype=torch.float64, device="cuda").normal_(generator=g)
+        out.append(hp.hphi_hv(ham, v))
+    assert float((out[0] - out[1]).abs().max()) <= 1e-13 * 26 * float(v.abs().max())
+    assert torch.equal(out[0], out[1]) != blocked
