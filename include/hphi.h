@@ -36,9 +36,11 @@
  *   * Unless stated otherwise calls are asynchronous on the HIP stream
  *     passed as `stream` (a hipStream_t; NULL = the legacy default stream).
  *   * Handles (hphi_basis, hphi_ham) are library-owned and immutable
- *     after build.  A hphi_ham holds a small reduction workspace:
- *     calls that share one hphi_ham must not overlap in time on
- *     different streams.
+ *     after build.  A hphi_ham holds a reduction workspace, so calls
+ *     that share one must not overlap in time on different streams.  On
+ *     sector bases it also holds tables of its operators: up to half an
+ *     8-byte vector of the space, or 16 MB where that is more.  Each
+ *     Hamiltonian and each observable has its own.
  */
 #ifndef HPHI_H
 #define HPHI_H
@@ -242,7 +244,8 @@ int hphi_hv(const hphi_ham* ham, const void* v, void* u, int64_t nvec, int32_t d
  * the per-tile kernel), microseconds per product call (9 ints in all).  If the
  * environment variable HPHI_TUNE_CACHE names a file, the choice is
  * appended there and reused by later processes for the same device,
- * space and operators.  Synchronizes `stream`. */
+ * space and operators.  Lines of a library without the class-blocked kernel
+ * are passed over for Hamiltonians that it serves.  Synchronizes `stream`. */
 int hphi_hv_tune(const hphi_ham* ham, const void* v, void* u, int64_t nvec, int32_t dtype,
                  int32_t* sched_out, void* stream);
 
@@ -287,7 +290,8 @@ int hphi_hv_cma_plan(const hphi_ham* ham, int32_t cluster_bits, int32_t* n_clust
  * of each gather it records the target index it decoded (for partners that
  * the windowed kernel takes from its LDS row tile or from another lane, the
  * partner's configuration as it arrives through that on-chip path) and the
- * signed element.  For rows row0 .. row0+nrows-1 (at most 2^22 per call)
+ * signed element.  The class-blocked sector kernel decodes nothing per call; its
+ * list is read from the tables that it gathers by.  For rows row0 .. row0+nrows-1 (at most 2^22 per call)
  * it then writes up to `cap` elements per row:
  *   the diagonal (col = row, term_id = -1, value = sum of diagonal parts) if nonzero,
  *   then one entry per packed off-diagonal operator whose element is nonzero,

@@ -163,7 +163,7 @@ struct GroupBuild {
     uint32_t* xnb;
 };
 
-// the groups of a basis and their device image (basis.cpp)
+// the groups of a basis and their device image (group.hip)
 void group_order(const hphi_basis* B, const std::vector<uint64_t>& h_val, const std::vector<uint32_t>& h_lobase,
                  const std::vector<uint32_t>& cls_off, const std::vector<uint32_t>& cls_count, GroupBasis& gb,
                  std::vector<char>& image);

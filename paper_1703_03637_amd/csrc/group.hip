@@ -293,7 +293,8 @@ bool group_analyse(const hphi_basis* B, const std::vector<DevOp>& ops, bool is_c
 // the high half come first: a segment of them holds at most about 96 MB of an
 // 8-byte vector, so the partner blocks of the operators on the other bits stay
 // in the 256 MB memory-side cache while the eight XCDs sweep the segment
-// together; inside it the charge classes, and inside a class ascending high
+// together.  The order is one for all row widths: with rows of 32 bytes a segment
+// is 384 MB and only part of it stays there.  Inside it the charge classes, and inside a class ascending high
 // halves in groups of K.  A group goes to the XCD with the fewest items so far,
 // whole, so that the blocks of a group are read through one L2.
 void group_order(const hphi_basis* B, const std::vector<uint64_t>& h_val, const std::vector<uint32_t>& h_lobase,

@@ -62,9 +62,10 @@ __device__ __forceinline__ void hvg_body(Args& A, const TailAt tail, const int b
     // bytes per lane.  Narrow FP32 rows are bound by the L1's in-order returns
     // (its pending stalls take 60-70% of the cycles) and lose with more in
     // flight per wave: 1.25e9 FP32 rows, K = 8, LL/LH/HH = 32/16/64 36.2 ms,
-    // 64/32/64 37.8, 128/64/64 60; rows of four scalars and more are bound by
+    // 64/32/64 37.8, 128/64/64 60; lanes of 16 bytes and more are bound by
     // the traffic between L2 and the fabric (6.2 TB/s on four complex64
-    // vectors) and want it full: 64/32/64 81.0 ms, 128/64/128 78.2.
+    // vectors) and want it full: 64/32/64 81.0 ms, 128/64/128 78.2.  One
+    // complex128 vector, a 16-byte lane of two scalars, goes with them.
     constexpr int LL = Ly::LB >= 16 ? 128 : sizeof(S) == 4 ? 32 : 64;
     constexpr int LH = Ly::LB >= 16 ? 64 : sizeof(S) == 4 ? 16 : 32;
     constexpr int HH = Ly::LB >= 16 ? 128 : 64;

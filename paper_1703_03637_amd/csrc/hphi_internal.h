@@ -413,7 +413,6 @@ int hv_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out);
 // blocks of a persistent grid dealt to problems in multiples of 8: begin[n + 1]
 // from the wavefront items of each (`groups`: groups of 8 blocks in all)
 std::vector<int> deal_blocks(const std::vector<int64_t>& items, int64_t groups);
-// the sums of a product from its block partials
 // the tail of a product of n_blocks blocks: what the kernel takes along, and
 // the launches that follow if it takes nothing
 // (sums_max: partials up to which plain sums stay in the kernel)

@@ -17,7 +17,8 @@
 //
 // Reductions: per row FP64 products, a per-tile wavefront reduce-scatter
 // (each lane ends up owning one vector's sum), a fixed-order block sum and
-// a fixed-order second-stage kernel.
+// the sums over the blocks in a fixed order, taken by the last block to
+// finish (tail.h) or, where the partials are many, by a second kernel.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
