@@ -390,21 +390,34 @@ int group_build(const hphi_basis* B, const GroupBuild& G) {
 //   rows of one or two scalars: 48,620 FP32 rows (932 wavefronts) 14 / 19 / 23 / 33;
 //     46,376 (3,693) 14.8 / 13.9 / 16.4 / 20; 376,740 (11,142) 22.5 / 18.4 / 17.1 /
 //     20.6; from 4,194,304 rows on 8: 20,058,300 FP64 rows 1,030 / 630 / 590 / 570
-//   rows of four: 48,620 complex128 x 2 20 / 24 / 34; 376,740 39 / 35 / 31; 853,776
-//     (15,196 wavefronts) 76 / 72 / 83; 2,704,156 133 / 126 / 131
+//   rows of four: 48,620 complex128 x 2 20 / 24 / 34; 184,756 (3,280) 37.4 / 40.3 /
+//     49.9; 376,740 39 / 35 / 31; 853,776 (15,196 wavefronts) 76 / 72 / 83; 2,704,156
+//     133 / 126 / 131
 //   wider rows: 63,504 complex64 x 8 (5,696) 25 / 19.5 / 26; 376,740 x 4 (22,284)
 //     51 / 47 / 40; 184,756 x 4 (6,560) 23.6 / 24.6 / 20.3
 // FP64 rows of 8 or 16 scalars have twice the lanes between 3,072 and 16,384
 // items, where four high halves leave a SIMD a wavefront or two of them (352,716
 // rows of 8 FP64 104 -> 79 us in the triangular, 72 -> 59 in the kagome lattice;
 // above, 2,035,800 rows lose, 439 -> 473 us).
+// Sparse FP64 sectors, at most 50 rows to an item, have short classes that leave part
+// of a tile idle:
+//   spins, 8 or 16 scalars, from 4,096 items: four at the plain lanes (134,596 rows of
+//     8 FP64, triangular lattice 67.5 -> 55.8; 296,010 146 -> 124; kagome 40 -> 34.7;
+//     3 of 28 sectors lose, by 3 to 8%).  Fermions hold the signs of each high half as
+//     well and lose 4 to 19% by it.
+//   spins, 8 scalars, 2,700 to 3,072 items, at most 25 rows each: one (53,130 rows 45.8
+//     -> 38.0; with 41 rows each two, 48 against 59).
+//   fermions, 16 and 32 scalars, from 2,048 items: two where full tiles take four
+//     (48,400 rows of 16 complex128 68 -> 56, of 8 44.7 -> 36.6; 218,400 of 16 205 -> 179);
+//     below, with at most 14 rows each, one (8,281 rows of 16 28 -> 20).
 struct GroupShape {
     int k, lanes;
 };
 
-static GroupShape group_shape(int ns, bool f64, int64_t items, bool large) {
+static GroupShape group_shape(int ns, bool f64, bool sign, int64_t items, int64_t rows) {
     GroupShape s{1, group_lanes(ns)};
     const int64_t waves = items * s.lanes;
+    const bool large = rows >= kGroupLarge, mid = f64 && ns >= 8 && ns <= 16 && items < 16384, sparse = f64 && rows <= 50 * items;
     if (const char* e = std::getenv("HPHI_GROUP_K")) {
         const int k = std::atoi(e);
         if (((k == 1 || k == 2) && !large) || k == 4 || (k == 8 && ns <= 2)) {
@@ -413,10 +426,14 @@ static GroupShape group_shape(int ns, bool f64, int64_t items, bool large) {
         }
     }
     if (large) s.k = ns <= 2 ? 8 : 4;
-    else if (waves < (ns == 4 ? 3200 : ns < 4 ? 3584 : 4096)) s.k = 1;
+    else if (waves < (ns < 4 ? 3584 : ns == 4 && !f64 ? 3200 : 4096)) s.k = 1;
     else if (ns <= 2) s.k = waves < 9216 ? 2 : 4;
     else if (ns == 4) s.k = 2;
-    else if (f64 && ns <= 16 && items >= 3072 && items < 16384) s = GroupShape{4, 2 * s.lanes};
+    else if (mid && sparse && !sign && items >= 4096) s.k = 4;
+    else if (mid && items >= 3072) s = GroupShape{4, 2 * s.lanes};
+    else if (mid && !sign && ns == 8 && rows <= 25 * items && items >= 2700) s.k = 1;
+    else if (sparse && sign && ns >= 16 && items >= 2048 && (ns > 16 || items < 4096)) s.k = 2;
+    else if (sign && f64 && ns >= 16 && rows <= 14 * items && items < 2048) s.k = 1;
     else s.k = waves < 6144 ? 2 : 4;
     return s;
 }
@@ -464,7 +481,7 @@ int try_launch_hvg(const HvLaunch& L, const Schedule& sc, hipStream_t st) {
     const bool cplx = dtype_complex(L.dtype), f64 = L.dtype == HPHI_F64 || L.dtype == HPHI_C128;
     if (L.ex && !cplx) return 1;
     const int ns = L.nvec * (cplx ? 2 : 1);
-    const GroupShape g = group_shape(ns, f64, B->grp.n_item, B->dim >= kGroupLarge);
+    const GroupShape g = group_shape(ns, f64, B->desc.particle == HPHI_FERMION, B->grp.n_item, B->dim);
     HvgArgs A{};
     group_args(H, g.k, cplx, A);
     A.v = L.v;
@@ -507,7 +524,7 @@ int group_multi_prepare(const HvLaunch* Ls, int n, MultiPlan* out) {
         rows += Ls[p].ham->basis->dim;
         n_item += Ls[p].ham->basis->grp.n_item;
     }
-    P.group_k = std::max(2, group_shape(ns, f64, n_item, rows >= kGroupLarge).k);
+    P.group_k = std::max(2, group_shape(ns, f64, false, n_item, rows).k);
     P.cc = false;
     std::vector<HvgArgs> args(n, HvgArgs{});
     std::vector<int64_t> items(n);

@@ -179,3 +179,30 @@ def test_tables_are_counted_as_they_are_allocated(monkeypatch, two_sz, split, bl
         out.append(hp.hphi_hv(ham, v))
     assert float((out[0] - out[1]).abs().max()) <= 1e-13 * 26 * float(v.abs().max())
     assert torch.equal(out[0], out[1]) != blocked
+
+
+SPARSE = {
+    "triangular24_up6": _torus(6, 4, 6), "triangular25_up5": _torus(5, 5, 5),
+    "hubbard4x3_3_3": (BasisDesc("fermion", 12, "nupndn", n_up=3, n_dn=3), L.hubbard_terms(L.rect_bonds(4, 3), 12, t=1.0, U=8.0)),
+    "hubbard7x2_2_2": (BasisDesc("fermion", 14, "nupndn", n_up=2, n_dn=2),
+                       L.hubbard_terms([b for b in L.rect_bonds(7, 2) if b[0] != b[1]], 14, t=1.0, U=8.0)),
+}
+
+
+@pytest.mark.parametrize("dt,nvec", [("c128", 2), ("f64", 8), ("c128", 8), ("c128", 16)])
+@pytest.mark.parametrize("name", list(SPARSE))
+def test_default_shapes_of_sparse_sectors_match_the_per_tile_kernel(monkeypatch, name, dt, nvec):
+    """Sectors with few rows to a tile have shapes of their own (1e-13 of the row sums of |H|: 0.75 per spin bond; for
+    fermions at most 4 hops of 1 per particle and U = 8 on at most 3 sites)."""
+    print(f"[gpu] sparse default shape {name} {dt} nvec={nvec}", flush=True)
+    desc, terms = SPARSE[name]
+    ham = hp.hphi_ham_build(hp.hphi_basis_build(desc), terms)
+    v = _vectors(ham.dim, nvec, dt)
+    out = []
+    for mode in ("2", "0"):
+        monkeypatch.setenv("HPHI_SECTOR_BLOCKS", mode)
+        red = torch.empty(4 * nvec, dtype=torch.float64, device="cuda")
+        out.append((hp.hphi_hv(ham, v, reduce=red).cpu().numpy().reshape(ham.dim, nvec), red.cpu().numpy()))
+    row = 0.75 * 75 if desc.particle == "spin" else 4 * 6 + 8 * 3
+    assert np.max(abs(out[0][0] - out[1][0])) <= 1e-13 * row * float(v.abs().max())
+    assert np.all(abs(out[0][1] - out[1][1]) <= 1e-12 * row ** 2 * out[1][1][:nvec].max())
